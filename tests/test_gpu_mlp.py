@@ -114,3 +114,40 @@ def test_gpu_training_reduces_loss():
         zf.mlp_adam(P, G, Md, Vd, s, lr=3e-3)
     zf.mlp_grad(P, Xd, Kd, Td, G, L, W)
     assert L.item() < 0.2 * l0
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 65, 127, 2049])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_tile_edges_and_unaligned_pointers(n, shift):
+    # sizes around the 16-sample (scores) and 64-sample (gradient) tiles, one
+    # output index out of range, and inputs that start 4 * shift bytes past a
+    # 16-byte boundary; tolerance as in the tests above
+    import torch
+
+    def put(a, dtype):
+        a = np.ascontiguousarray(a, dtype=dtype)
+        buf = torch.zeros(a.size + 4, dtype=torch.from_numpy(a.reshape(-1)[:1]).dtype, device="cuda")
+        v = buf[shift:shift + a.size].view(a.shape)
+        v.copy_(torch.from_numpy(a))
+        return v
+    p32 = M.he_uniform(n).astype(np.float32)
+    X, k, t = batch(n + 1, n)
+    P, Xd, Td = put(p32, np.float32), put(X, np.float32), put(t, np.float32)
+    Y = torch.full((n + 1, 24), 5.0, dtype=torch.float32, device="cuda")
+    zf.mlp_forward(P, Xd, Y[:n])
+    _, yref = M.forward(p32.astype(np.float64), X.astype(np.float64))
+    assert np.abs(Y[:n].cpu().numpy() - yref).max() <= 1e-5 * max(1.0, np.abs(yref).max())
+    assert torch.all(Y[n] == 5.0)
+    G = torch.empty(M.n_params(), dtype=torch.float32, device="cuda")
+    L = torch.empty(1, dtype=torch.float32, device="cuda")
+    W = torch.full((zf.mlp_grad_work_bytes(n) // 4 + 1,), 5.0, dtype=torch.float32, device="cuda")
+    bad = k.copy()
+    bad[n // 2] = -1
+    zf.mlp_grad(P, Xd, put(bad, np.int32), Td, G, L, W[:-1])
+    assert np.isnan(L.item()) and W[-1].item() == 5.0
+    tref = t.astype(np.float64)
+    tref[n // 2] = yref[n // 2, k[n // 2]]  # no error, so no gradient from that sample
+    _, gref = M.grad(p32.astype(np.float64), X.astype(np.float64), k, tref)
+    g = G.cpu().numpy().astype(np.float64)
+    for a, b in zip(tensors(g), tensors(gref)):
+        assert np.linalg.norm(a - b) <= 1e-5 * max(np.linalg.norm(b), 1e-30)
