@@ -59,13 +59,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(W / 2, W /
 }
 template <uint32_t W>
 static void launch_sdict_hot(const LaunchArgs &A, uint32_t n, hipStream_t st) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode_sdict_hot<W>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, int(kSdHotLds));
-    const uint32_t blocks = min(2u * uint32_t(cus), (n + W - 1) / W);
+    const uint32_t blocks = min(2u * cu_count(), (n + W - 1) / W);
     hipLaunchKernelGGL(k_decode_sdict_hot<W>, dim3(blocks), dim3(64 * W), kSdHotLds, st, A);
 }
 void launch_sdict(const LaunchArgs &A, uint32_t waves, hipStream_t st) {

@@ -1832,17 +1832,34 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 // ===================================================================== ANS
 // One wave decodes one chunk: lane j runs coder j, which holds bytes j,
 // j + 64, j + 128, ... (Sec. 3.1 sees ANS as one serial state chain per chunk;
-// the 64 interleaved chains of a chunk advance in lockstep).  Per wave the LDS
-// holds the model: slot -> byte (4096 bytes) and byte -> {f, cum} (256 dwords).
-// The coders share one stream of 16-bit words, read in byte order: at each
-// step the lanes whose state fell below L take the next words in lane order
-// (a ballot and a count of the set bits below each lane).  The wave keeps a
-// window of 128 words in registers (lane l: words base + l and base + 64 + l,
-// packed in one dword) and reads a lane's word with one cross-lane permute;
-// the 64 words after the window are loaded one slide ahead, so the stream is
-// read once, in coalesced 128-byte loads.
-// lds: this wave's kAnsLdsWords dwords (the last 256: output staging).
-ZF_DEV void unit_ans(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
+// the 64 interleaved chains of a chunk advance in lockstep).  The coders
+// share one stream of 16-bit words, read in byte order: at each step the lanes
+// whose state fell below L take the next words in lane order (a ballot and a
+// count of the set bits below each lane).  The stream is read once, in
+// coalesced loads one refill ahead, into a ring of kAnsRing words in the
+// wave's LDS whose first 64 words stand after its end again, so that a step
+// reads lane by lane from a uniform offset on.
+//
+// A step is a chain: state -> slot -> model -> state -> who needs a word ->
+// word -> state.  What a chunk costs is that chain's latency while few waves
+// share a SIMD, and the instructions issued per step when many do, so there
+// are two models:
+//   FUSED: one dword per slot {byte, slot - cum, f - 1}, 16 KiB: one LDS
+//     read between the slot and the next state, and the ring holds each word
+//     with the table address it leads to beside it, so that the address is
+//     known two instructions after the word.  Eight waves fit a CU's LDS.
+//   else: slot -> byte (4 KiB) and byte -> {f, -cum} (2 KiB): two reads, but
+//     19 waves a CU.
+// 64 KiB chunks of flags, one wave a CU: 150 us with two reads, a ring in
+// registers read by cross-lane permutes and 1.4 times the instructions, 129 us
+// with two reads and this ring, 97 us fused.  4,096 chunks (16 waves a CU, the
+// LDS about 26 cycles a step and wave): 199 -> 179 us.
+constexpr uint32_t kAnsRing = 512;        // words; a refill brings half of them
+constexpr uint32_t kAnsSteps = 4;         // steps between two looks at the ring (at most 64 words each)
+static_assert(kAnsSteps * kAnsLanes <= kAnsRing / 2, "ANS ring");
+
+template <bool FUSED>
+ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t lane = lane_id();
     const uint32_t es = ck.dtype == D_I32 ? 4 : (ck.dtype == D_I64 || ck.dtype == D_F64) ? 8
@@ -1860,85 +1877,132 @@ ZF_DEV void unit_ans(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    uint8_t *sym = reinterpret_cast<uint8_t *>(lds);
-    uint32_t *fc = lds + kAnsM / 4;
+    // the shared words through a bounds-checked view of the stream, whole
+    // dwords (a word past an odd end is read by a corrupt stream only); lane
+    // l of refill h loads words [256 h + 4 l, + 4)
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(uniform_ptr(s + kAnsHdr)), 0, int((2 * nw + 3) & ~3u), 0x00020000);
+    uint32_t pre0, pre1;
+    auto load = [&](uint32_t at) {
+        pre0 = __builtin_amdgcn_raw_buffer_load_b32(rw, int(2 * (at + 4 * lane)), 0, 0);
+        pre1 = __builtin_amdgcn_raw_buffer_load_b32(rw, int(2 * (at + 4 * lane) + 4), 0, 0);
+    };
+    load(0);
+    uint32_t x = ld32u(s + 528 + 4 * lane);  // this coder's state
     // model: lane l owns bytes 4l .. 4l + 3
     const uint32_t f2 = ld32u(s + 16 + 8 * lane), f3 = ld32u(s + 20 + 8 * lane);
     const uint32_t f[4] = {f2 & 0xFFFFu, f2 >> 16, f3 & 0xFFFFu, f3 >> 16};
     const uint32_t tot = f[0] + f[1] + f[2] + f[3];
     const uint32_t cincl = scan_add32(tot);
-    if (rl32(cincl, 63) != kAnsM) {  // the slot walk below needs the exact total
+    if (rl32(cincl, 63) != kAnsM) {  // every slot must belong to a byte
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    uint32_t c = cincl - tot;  // cum of byte 4l
-#pragma unroll
-    for (uint32_t k = 0; k < 4; k++) {
-        fc[4 * lane + k] = f[k] | (c << 16);
-        c += f[k];
-    }
-    wave_fence();
-    // slot -> byte: lane l fills slots [64 l, 64 l + 64), walking the bytes
-    // from the one holding slot 64 l (a binary search over cum)
+    uint32_t *tab = lds;                                                  // FUSED: slot -> entry
+    uint8_t *sym = reinterpret_cast<uint8_t *>(lds);                      // else: slot -> byte
+    u32x2 *fc = reinterpret_cast<u32x2 *>(lds + kAnsM / 4);               // and byte -> {f, -cum}
+    uint32_t *ring = lds + (FUSED ? kAnsM : kAnsM / 4 + 512);
+    constexpr uint32_t kWordBytes = FUSED ? 4 : 2;                        // of a ring entry
+    uint8_t *stg = reinterpret_cast<uint8_t *>(ring) + (kAnsRing + 64) * kWordBytes;  // 1 KiB of output
     {
-        const uint32_t s0 = 64 * lane;
-        uint32_t lo = 0, hi = 256;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if ((fc[mid] >> 16) <= s0) lo = mid;
-            else hi = mid;
-        }
-        uint32_t b = lo, e = (fc[b] >> 16) + (fc[b] & 0xFFFFu);
-        for (uint32_t k = 0; k < 64; k += 4) {
-            uint32_t word = 0;
+        // Slot -> byte: bit c - 1 of a 4096-bit map is set for every present
+        // byte whose slots start at c > 0, so the bits below a slot count
+        // its byte's rank among the present ones; row k of 64 slots is a
+        // wave's lanes.  (The map and the ranked list lie where the ring and
+        // the staging will.)
+        uint32_t *list = ring, *map = ring + 256;
+        map[lane] = 0;
+        map[64 + lane] = 0;
+        wave_fence();
+        const uint32_t here = (f[0] != 0) + (f[1] != 0) + (f[2] != 0) + (f[3] != 0);
+        uint32_t rank = scan_add32(here) - here, c = cincl - tot;  // of byte 4l
 #pragma unroll
-            for (uint32_t i = 0; i < 4; i++) {
-                while (s0 + k + i >= e) {  // next byte with a nonzero frequency
-                    b++;
-                    e = (fc[b] >> 16) + (fc[b] & 0xFFFFu);
-                }
-                word |= b << (8 * i);
+        for (uint32_t k = 0; k < 4; k++) {
+            const uint32_t b = 4 * lane + k;
+            if (f[k]) {
+                list[rank] = FUSED ? b + ((f[k] - 1) << 20) - (c << 8) : b;
+                if (c)
+                    __hip_atomic_fetch_or(map + ((c - 1) >> 5), 1u << ((c - 1) & 31u), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+                rank++;
             }
-            *reinterpret_cast<uint32_t *>(sym + s0 + k) = word;
+            if constexpr (!FUSED) fc[b] = u32x2{f[k], 0u - c};
+            c += f[k];
+        }
+        wave_fence();
+        const uint32_t mlo = map[2 * lane], mhi = map[2 * lane + 1];
+        const uint32_t bits = uint32_t(__popc(mlo) + __popc(mhi)), below = scan_add32(bits) - bits;
+#pragma unroll 8
+        for (uint32_t k = 0; k < 64; k++) {
+            const uint32_t r = __builtin_amdgcn_mbcnt_hi(
+                rl32(mhi, k), __builtin_amdgcn_mbcnt_lo(rl32(mlo, k), rl32(below, k)));
+            const uint32_t v = list[r], slot = 64 * k + lane;
+            if constexpr (FUSED) tab[slot] = v + (slot << 8);
+            else sym[slot] = uint8_t(v);
         }
     }
     wave_fence();
-    // this coder's state; the shared words through a bounds-checked view of
-    // the stream (0 past its end, which only a corrupt stream reaches)
-    uint32_t x = ld32u(s + 528 + 4 * lane);
-    const __amdgpu_buffer_rsrc_t rw =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(s + kAnsHdr), 0, int(2 * nw), 0x00020000);
-    auto ld16 = [&](uint32_t at) { return uint32_t(__builtin_amdgcn_raw_buffer_load_b16(rw, int(2 * at), 0, 0)); };
-    // window: words [base, base + 128) in win (lane l: base + l low, base + 64
-    // + l high); ahead: word base + 128 + l.  pos - base < 64 at every step's
-    // start, so a step's at most 64 words lie inside the window.
-    uint32_t pos = 0, base = 0;
-    uint32_t win = ld16(lane) | (ld16(64 + lane) << 16);
-    uint32_t ahead = ld16(128 + lane);
+    uint32_t pos = 0, filled = 0;  // words taken; words brought into the ring
+    auto refill = [&]() {
+        // words [filled, filled + 256) into their half of the ring
+        const uint32_t at = (filled & (kAnsRing - 1)) + 4 * lane;
+        if constexpr (FUSED) {
+            // the word above the table address of the slot it ends in
+            const u32x4 v = {(pre0 << 16) | ((pre0 << 2) & 0x3FFCu), (pre0 & 0xFFFF0000u) | ((pre0 >> 14) & 0x3FFCu),
+                             (pre1 << 16) | ((pre1 << 2) & 0x3FFCu), (pre1 & 0xFFFF0000u) | ((pre1 >> 14) & 0x3FFCu)};
+            *reinterpret_cast<u32x4 *>(ring + at) = v;
+            if (at < 64) *reinterpret_cast<u32x4 *>(ring + kAnsRing + at) = v;
+        } else {
+            const u32x2 v = {pre0, pre1};
+            *reinterpret_cast<u32x2 *>(ring + at / 2) = v;
+            if (at < 64) *reinterpret_cast<u32x2 *>(ring + (kAnsRing + at) / 2) = v;
+        }
+        filled += kAnsRing / 2;
+        load(filled);
+        wave_fence();
+    };
+    refill();
+    refill();
+    // FUSED: the model's entry of x's slot, read as soon as its address is
+    // known (at the end of the step before)
+    auto entry = [&](uint32_t a) {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(tab) + (a & 0x3FFCu));
+    };
+    uint32_t e0 = FUSED ? entry(x << 2) : 0u;
+    // one byte per coder: b's low byte
     auto step = [&](uint32_t &b, bool act) {
-        const uint32_t slot = x & (kAnsM - 1);
-        b = sym[slot];
-        const uint32_t e = fc[b];
-        const uint32_t xn = (e & 0xFFFFu) * (x >> 12) + slot - (e >> 16);
+        uint32_t xn;
+        if constexpr (FUSED) {
+            b = e0;
+            const uint32_t xs = x >> 12;
+            uint32_t off = xs + ((b >> 8) & 0xFFFu);
+            asm volatile("" : "+v"(off));  // (one multiply-add after the frequency)
+            xn = (b >> 20) * xs + off;
+        } else {
+            const uint32_t slot = x & (kAnsM - 1);
+            b = sym[slot];
+            const u32x2 e = fc[b];
+            xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
+        }
         x = act ? xn : x;
         const bool need = act && x < kAnsL;  // one word at most: x >= 1 * 2^4 before the shift
         const uint64_t m = __ballot(need);
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-        const uint32_t j = pos - base + rank;  // < 128
-        // (the permute reads lane (address / 4) mod 64)
-        const uint32_t pair = uint32_t(__builtin_amdgcn_ds_bpermute(int(j << 2), int(win)));
-        // (x << 16) | (the low or high half of pair) in one byte permute
-        const uint32_t sel = 0x05040100u + ((j >> 5) & 2u) * 0x0101u;
-        // (computed by every lane and selected: a branch around it costs more)
-        uint32_t xp = __builtin_amdgcn_perm(x, pair, sel);
-        asm volatile("" : "+v"(xp));
-        x = need ? xp : x;
-        pos += uint32_t(__popcll(m));
-        if (pos - base >= 64) {  // slide by 64 words
-            base += 64;
-            win = (win >> 16) | (ahead << 16);
-            ahead = ld16(base + 128 + lane);
+        const uint32_t p0 = pos & (kAnsRing - 1);
+        // (read by every lane and selected: a branch around it costs more)
+        if constexpr (FUSED) {
+            const uint32_t e = ring[p0 + rank];
+            e0 = entry(need ? e : x << 2);
+            __builtin_amdgcn_sched_barrier(0);  // the next step's read before this state's last words
+            const uint32_t xp = alignbit(x, e, 16);
+            x = need ? xp : x;
+        } else {
+            const uint32_t w = reinterpret_cast<const uint16_t *>(ring)[p0 + rank];
+            uint32_t xp = (x << 16) | w;
+            asm volatile("" : "+v"(xp));
+            x = need ? xp : x;
         }
+        pos += uint32_t(__popcll(m));
     };
     bool bad = false;
     const uint32_t steps = (n + kAnsLanes - 1) / kAnsLanes;
@@ -1946,10 +2010,10 @@ ZF_DEV void unit_ans(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
     if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
         // 16 steps at a time: each lane's 16 bytes (one per step, 64 apart)
         // gathered in LDS, then written back as 16 contiguous bytes per lane
-        uint8_t *stg = reinterpret_cast<uint8_t *>(lds + kAnsLdsWords - 256);
         for (; t + 16 <= n / kAnsLanes; t += 16) {
 #pragma unroll
             for (uint32_t jj = 0; jj < 16; jj++) {
+                if (jj % kAnsSteps == 0 && pos + kAnsRing / 2 > filled) refill();
                 uint32_t b;
                 step(b, true);
                 stg[64 * jj + lane] = uint8_t(b);
@@ -1961,6 +2025,7 @@ ZF_DEV void unit_ans(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
         }
     }
     for (; t < steps; t++) {
+        if (pos + kAnsRing / 2 > filled) refill();
         const uint32_t i = t * kAnsLanes + lane;
         uint32_t b;
         step(b, i < n);
@@ -2032,7 +2097,7 @@ ZF_DEV void run_unit(const LaunchArgs &A, uint32_t kind, uint32_t u, uint32_t *l
         break;
     case K_LZ: unit_lz<4>(A, ck, lz_row); break;
     case K_SDICT: unit_sdict<false>(A, t, ck, lz_row); break;
-    case K_ANS: unit_ans(A, ck, lz_row); break;
+    case K_ANS: unit_ans_t<false>(A, ck, lz_row); break;
     }
 }
 
@@ -2106,6 +2171,15 @@ hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const u
                          uint32_t lz_blk, hipStream_t st, KindEvents *ev);
 
 void launch_ans(const LaunchArgs &A, uint32_t waves, hipStream_t st);
+
+// Compute units of the current device.
+inline uint32_t cu_count() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return uint32_t(cus);
+}
 
 // Host launchers, one per kind, each defined in its kind's translation unit.
 #define ZF_KIND_LAUNCHERS(X)                                                                       \

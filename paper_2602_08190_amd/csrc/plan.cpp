@@ -200,9 +200,25 @@ static uint64_t table_bytes(const WorkTables &w) {
     return align_up(n, 256);
 }
 
+// Output bytes of a whole-chunk unit.
+static uint64_t unit_bytes(const ChunkDesc &c) { return uint64_t(c.n_elems) * elem_size(c.dtype); }
+
+// A wave decodes a whole ANS or LZ77 chunk, so a long one taken up last would
+// run on alone: the longest first (in chunk order where they are equal).
+static void longest_first(WorkTables &w) {
+    for (Kind k : {K_LZ, K_ANS}) {
+        auto longer = [&](const Tile &a, const Tile &b) {
+            return unit_bytes(w.chunks[a.chunk]) > unit_bytes(w.chunks[b.chunk]);
+        };
+        std::vector<Tile> &T = w.tiles[k];
+        if (!std::is_sorted(T.begin(), T.end(), longer)) std::stable_sort(T.begin(), T.end(), longer);
+    }
+}
+
 // Copy a launch's tables into host staging at `off`; fill its LaunchArgs.
-static void flatten(const WorkTables &w, std::vector<uint8_t> &host, uint64_t off, uint8_t *d_base,
+static void flatten(WorkTables &w, std::vector<uint8_t> &host, uint64_t off, uint8_t *d_base,
                     LaunchArgs &A) {
+    longest_first(w);
     uint8_t *h = host.data() + off;
     std::memcpy(h, w.chunks.data(), w.chunks.size() * sizeof(ChunkDesc));
     A.chunks = reinterpret_cast<const ChunkDesc *>(d_base + off);
@@ -220,6 +236,13 @@ static void flatten(const WorkTables &w, std::vector<uint8_t> &host, uint64_t of
     for (const Tile &t : w.tiles[K_SDICT]) {
         const uint32_t c = w.chunks[t.chunk].codec;
         A.sdict_codecs |= c == C_SDICT_COL || c == C_SDICT_COL_ANS ? 1u : 2u;
+    }
+    A.ans_load = 0;
+    if (!w.tiles[K_ANS].empty()) {
+        uint64_t sum = 0;
+        for (const Tile &t : w.tiles[K_ANS]) sum += unit_bytes(w.chunks[t.chunk]);
+        const uint64_t most = std::max<uint64_t>(1, unit_bytes(w.chunks[w.tiles[K_ANS][0].chunk]));
+        A.ans_load = uint32_t(sum / most);
     }
 }
 
@@ -371,7 +394,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     const int ns = o.n_slots;
     if (!P->batches.empty()) {
         P->d_slots.assign(std::min<size_t>(ns, P->batches.size()), nullptr);
-        for (auto &sp : P->d_slots) ZF_HIP(hipMalloc(&sp, slot));
+        for (auto &sp : P->d_slots) ZF_HIP(hipMalloc(&sp, align_up(slot, 256)));  // (whole dwords at its end)
     }
     if (dict_total) ZF_HIP(hipMalloc(&P->d_dict, dict_total));
     if (!fat.empty()) {

@@ -16,8 +16,9 @@ constexpr uint32_t kScratchCol = kMaxCols - 1;
 // ANS: M = 2^12 model, state in [2^16, 2^32), 64 interleaved coders, stream
 // header of 16 + 512 (frequencies) + 256 (states) + 256 (word offsets) bytes.
 constexpr uint32_t kAnsM = 4096, kAnsL = 65536, kAnsLanes = 64, kAnsHdr = 784;
-// ANS: LDS per wave, the model (1280 dwords) and 1 KiB of output staging
-constexpr uint32_t kAnsLdsWords = 1536;
+// ANS: LDS dwords per wave: the model (4 KiB and 2 KiB, or 16 KiB fused), the
+// word ring (576 entries of 2 or 4 bytes) and 1 KiB of output staging
+constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 4096 + 576 + 256;
 // String-dictionary: longest token
 constexpr uint32_t kSdMaxToken = 64;
 
@@ -98,6 +99,7 @@ struct LaunchArgs {
     uint32_t kind_begin[K_COUNT + 1];
     uint32_t two_stage;           // some units read the scratch area that earlier kinds write
     uint32_t sdict_codecs;        // String-dictionary tiles: bit 0 some over a column dictionary, bit 1 some not
+    uint32_t ans_load;            // bytes of all ANS tiles / bytes of the largest
 };
 
 // Host side: events recorded around each kind's launch of a profiled decode
