@@ -282,7 +282,9 @@ typedef enum {
  * over contiguous ranges of units, each sharing an LDS copy of the hottest
  * records of a column dictionary and staging through 2 KiB buffers, and
  * the other units in a second launch of 4-wave workgroups).  A lane always owns 16 output bytes per
- * step (C).  Zero fields take the tune cache's value, else a default. */
+ * step (C).  Zero fields take the tune cache's value, else a default, made
+ * smaller where a launch holds too little of the kind to fill the GPU with it
+ * (a fixed rule of the launch's size). */
 typedef struct {
     uint32_t unit;
     uint32_t waves_per_block;
@@ -364,8 +366,9 @@ zf_status zf_johnson_order(const double *a, const double *b, uint32_t n, uint32_
  * LZ77 and ANS: 0, 0, 0 (the whole stream).  A two-stage chunk lists its
  * first-stage units first (ANS pieces of SDICT_ANS / SDICT_COL_ANS, the run
  * starts of DSTREE in RLE32 / RLE64), then the units of its output stage.
- * Tiles come from opts (nullable: the tune cache, as zf_plan takes them)
- * and the chunk's schedule hint.  units: caller-owned host array of cap
+ * Tiles come from opts (nullable: the tune cache) and the chunk's schedule
+ * hint; zf_plan starts from the same tiles and, where opts leave a field zero,
+ * cuts smaller units for a launch that would not fill the GPU.  units: caller-owned host array of cap
  * entries; with units NULL and cap 0 only *n_units is set.  Host only, no
  * device needed.  Errors: ZF_E_INVALID (null column or n_units, chunk out
  * of range), ZF_E_TOO_SMALL (cap below the unit count).

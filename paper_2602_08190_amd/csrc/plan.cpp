@@ -171,6 +171,70 @@ static void add_chunk(WorkTables &w, const zf_column &col, uint32_t ci, uint32_t
     w.t_dec += double(c.plain_len) / (ts.rate_gbps[k] * 1e9);
 }
 
+// What a launch holds of each kind, in the measure of the kind's unit: blocks
+// of 2048 values (FP), elements (GP), bytes (PLAIN, SDICT), chunks (NP).
+struct KindLoad {
+    uint64_t n[K_COUNT] = {};
+    void add(const zf_column &col, uint32_t ci) {
+        const ChunkInfo &c = col.view.chunks[ci];
+        const Kind k = kind_of(c.codec, col.view.dtype);
+        switch (k) {
+        case K_PLAIN:
+        case K_SDICT: n[k] += c.plain_len; break;
+        case K_RLE32:
+        case K_RLE64: n[k] += c.n_elems; break;
+        case K_TREE:
+            n[k] += c.n_elems;
+            n[col.view.dtype == D_I32 ? K_RLE32 : K_RLE64] += rd32(col.buf.p + c.comp_off);  // the run starts
+            break;
+        case K_LZ:
+        case K_ANS: n[k] += 1; break;
+        default: n[k] += (c.n_elems + kForBlock - 1) / kForBlock;
+        }
+    }
+};
+
+// The tile shape of one launch.  The tune cache holds the shapes that were
+// fastest on gigabytes; what a launch of less takes is the time of one unit as
+// long as its units do not fill the GPU, so a kind's unit shrinks until the
+// launch has 8,192 of them or more (32 waves on each of 256 compute units; 4,096
+// String-dictionary units, whose prologue is long), and a workgroup holds no
+// more waves than leaves two workgroups per compute unit.  Shapes the caller
+// set stay.  Units of 256 elements, 1,024 bytes of tokens, one block and 8 KiB
+// of plain copy are the smallest: smaller ones were no faster.  Measured, with
+// the cache's shape and this rule's:
+//   String-dictionary, 1.5 MB 81 -> 10.5 us, 16 MiB 83 -> 20, 64 MiB 86 -> 46
+//   DSTREE output, 3 M keys 25 -> 10 us; RLE32, 300,000 dates 10.2 -> 7.0
+//   Float2Int, 300,000 doubles 36 -> 12.4 us; DICT128, 300,000 16.4 -> 13.6
+// The String-dictionary workgroups of 14 and 16 waves, which first fill an
+// LDS copy of the hottest records, pay from 1 GiB of output on (1 GiB 631 ->
+// 621 us, 2 GiB 1,265 -> 1,240; 512 MiB 264 -> 311, 256 MiB 141 -> 166).
+static uint64_t pow2_floor(uint64_t x) { return x ? uint64_t(1) << (63 - __builtin_clzll(x)) : 0; }
+static TileShape fit_tiles(TileShape t, const zf_plan_opts &o, const KindLoad &L, uint32_t cus) {
+    for (uint32_t k = 0; k < K_COUNT; k++) {
+        if (k == K_LZ || k == K_ANS) {  // (a unit is a whole chunk; LZ77's `unit` is its copy step's block)
+            if (!o.tiles[k].waves_per_block)
+                t.wpb[k] = uint32_t(std::clamp<uint64_t>(pow2_floor(L.n[k] / (2 * cus)), 1, t.wpb[k]));
+            continue;
+        }
+        const bool sd = k == K_SDICT, gp = k == K_RLE32 || k == K_RLE64 || k == K_TREE;
+        const bool hot = sd && t.wpb[k] >= 14;
+        if (hot && !o.tiles[k].waves_per_block && L.n[k] < (1ull << 30)) {
+            t.wpb[k] = 4;
+            if (!o.tiles[k].unit) t.unit[k] = std::min(t.unit[k], 16384u);
+        }
+        if (!o.tiles[k].unit) {
+            const uint32_t least = k == K_PLAIN ? 8192u : sd ? 1024u : gp ? 256u : 1u;
+            uint64_t u = L.n[k] / ((sd ? 16u : 32u) * cus);
+            u = pow2_floor(u);  // (as the cache's)
+            if (u < t.unit[k]) t.unit[k] = uint32_t(std::clamp<uint64_t>(u, std::min(least, t.unit[k]), t.unit[k]));
+        }
+        if (!o.tiles[k].waves_per_block && !(sd && t.wpb[k] >= 14))
+            t.wpb[k] = uint32_t(std::clamp<uint64_t>(pow2_floor(L.n[k] / t.unit[k] / (2 * cus)), 1, t.wpb[k]));
+    }
+    return t;
+}
+
 // Johnson's rule (Sec. 3.3): batches whose copy is shorter than their decode
 // first, by increasing copy time; the rest by decreasing decode time; equal
 // keys keep the lower batch index first (stable sorts of ascending indices).
@@ -274,7 +338,6 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     hipDeviceProp_t prop;
     ZF_HIP(hipGetDeviceProperties(&prop, device));
     P->cu_count = uint32_t(prop.multiProcessorCount);
-    for (uint32_t k = 0; k < K_COUNT; k++) P->waves_per_block[k] = ts.wpb[k];
     P->lz_blk = ts.unit[K_LZ];
     P->persistent_waves = o.persistent ? P->cu_count * ts.wpcu : 0;
 
@@ -296,12 +359,18 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
         at = align_up(at + cols[c]->buf.n, 256);
     }
     P->image_bytes = at;
+    KindLoad load;
+    for (uint32_t c = 0; c < n_cols; c++)
+        for (uint32_t i = 0; i < cols[c]->view.n_chunks; i++) load.add(*cols[c], i);
+    const TileShape its = fit_tiles(ts, o, load, P->cu_count);
+    std::copy(its.wpb, its.wpb + K_COUNT, image.wpb);
     for (uint32_t c = 0; c < n_cols; c++) {
         const zf_column &col = *cols[c];
         for (uint32_t i = 0; i < col.view.n_chunks; i++)
             add_chunk(image, col, i, c, P->image_off[c] + col.view.chunks[i].comp_off,
-                      P->image_off[c] + col.view.dict_off, ts, fat_at[c]);
+                      P->image_off[c] + col.view.dict_off, its, fat_at[c]);
     }
+    std::copy(image.wpb, image.wpb + K_COUNT, P->image_wpb);
 
     // ---- staged mode: dictionaries, then batches of whole chunks
     std::vector<uint64_t> dict_at(n_cols, 0);
@@ -326,8 +395,22 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     int64_t range_col = -1;
     uint64_t range_src = 0, range_dst = 0;  // current contiguous copy
     uint32_t range_next_chunk = 0;
+    struct Placed {
+        uint32_t col, chunk;
+        uint64_t dst;
+    };
+    std::vector<Placed> placed;  // the current batch's chunks
     auto close = [&]() {
-        if (!cur.w.chunks.empty()) batches.push_back(std::move(cur));
+        if (!placed.empty()) {
+            KindLoad load;
+            for (const Placed &p : placed) load.add(*cols[p.col], p.chunk);
+            const TileShape bts = fit_tiles(ts, o, load, P->cu_count);
+            std::copy(bts.wpb, bts.wpb + K_COUNT, cur.w.wpb);
+            for (const Placed &p : placed)
+                add_chunk(cur.w, *cols[p.col], p.chunk, p.col, p.dst, dict_at[p.col], bts, fat_at[p.col]);
+            batches.push_back(std::move(cur));
+        }
+        placed.clear();
         cur = Batch{};
         range_col = -1;
     };
@@ -352,7 +435,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
             cur.copies.back().len = ch.comp_off + ch.comp_len - range_src;
             cur.slot_used = dst + ch.comp_len;
             range_next_chunk = i + 1;
-            add_chunk(cur.w, col, i, c, dst, dict_at[c], ts, fat_at[c]);
+            placed.push_back({c, i, dst});
         }
     }
     close();
@@ -447,7 +530,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
         try {
             for (auto &b : P->batches) {
                 ZF_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-                hipError_t le = launch_decode(b.args, P->persistent_waves, P->waves_per_block, P->lz_blk, cap);
+                hipError_t le = launch_decode(b.args, P->persistent_waves, b.w.wpb, P->lz_blk, cap);
                 hipError_t ce = hipStreamEndCapture(cap, &b.graph);
                 ZF_HIP(le);
                 ZF_HIP(ce);

@@ -22,6 +22,7 @@ struct CopyOp {
 struct WorkTables {
     std::vector<ChunkDesc> chunks;
     std::vector<Tile> tiles[K_COUNT];
+    uint32_t wpb[K_COUNT] = {};  // waves per workgroup
     uint64_t plain_bytes = 0, comp_bytes = 0;
     uint64_t scratch_bytes = 0;  // scratch area the launch's two-stage chunks use
     double t_dec = 0;  // decode-time estimate, seconds
@@ -57,7 +58,7 @@ struct zf_plan {
     // launch configuration
     uint32_t persistent_waves = 0;  // 0: per-kind launches
     uint32_t lz_blk = 16;         // LZ77 bytes per block
-    uint32_t waves_per_block[zf::K_COUNT] = {4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4};
+    uint32_t image_wpb[zf::K_COUNT] = {};  // waves per workgroup of the image's launches
     uint32_t cu_count = 0;
 
     // device memory

@@ -7,7 +7,7 @@ from paper_2602_08190_amd import datagen as g
 from paper_2602_08190_amd import zf
 
 from conftest import gpu_available
-from test_gpu_parity import check, decode_image, log, torch
+from test_gpu_parity import check, decode_image, decode_staged, log, torch
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
@@ -59,3 +59,27 @@ def test_ans_long_chunks(size):
     col, x = ans_mix(15, size)
     check([col], decode_image([col]), [x])
     check([col], decode_image([col], persistent=True), [x])
+
+
+@pytest.mark.parametrize("d", [-1, 0, 1])
+def test_smallest_units(d):
+    # columns of one smallest unit of each kind (2048 values, 256 elements,
+    # 1,024 bytes of text, 8 KiB of plain copy) and a few, give or take one
+    # value, planned with the default tiles
+    cols, xs = [], []
+    for k in (1, 3, 40):
+        nb, ne, nt = 2048 * k + d, 256 * k + d, 1024 * k + d
+        r = g.rng(100 * k + d)
+        xs += [r.integers(-5, 10 ** 6, size=nb).astype(np.int32), r.integers(-5, 10 ** 6, size=nb),
+               g.fixed16_column(nb, 30, k), r.integers(0, 7, size=nb).astype(np.int32), r.integers(0, 7, size=nb),
+               g.decimal_column(nb, k, 100, 10 ** 6), g.sorted_runs_column(ne, 3, k),
+               g.sorted_runs_column(ne, 3, k, dtype=np.int64), g.key_column(ne, k), g.orderkey_column(ne, k),
+               g.text_column(nt, k), g.text_column(nt, k), g.text_column(nt, k),
+               np.frombuffer(r.bytes(8192 * k + d), np.uint8)]
+        codecs = [zf.FOR_BP, zf.FOR_BP, zf.DICT_BP, zf.DICT_BP, zf.DICT_BP, zf.F2I_BP, zf.RLE_DELTA_BP, zf.DELTA_BP,
+                  zf.DSTRIDE_BP, zf.DSTREE, zf.SDICT_BP, zf.SDICT_COL, zf.SDICT_COL_ANS, zf.PLAIN]
+        cols += [zf.Column.compress(x, c) for x, c in zip(xs[-14:], codecs)]
+    check(cols, decode_image(cols), xs)
+    for slot in (1 << 14, 1 << 20):
+        outs, _ = decode_staged(cols, slot_bytes=slot)
+        check(cols, outs, xs)
