@@ -225,11 +225,32 @@ ZF_DEV uint32_t alignbit(uint32_t hi, uint32_t lo, uint32_t s) {
     return __builtin_amdgcn_alignbit(hi, lo, s);
 }
 
+// 10^e and the double nearest 1 / 10^e, e = 0..18.
+struct F2iScale {
+    double div, rcp;
+};
+ZF_DEV F2iScale f2i_scale(uint32_t e) {
+    constexpr double kPow10[19] = {1e0,  1e1,  1e2,  1e3,  1e4,  1e5,  1e6,  1e7,  1e8, 1e9,
+                                   1e10, 1e11, 1e12, 1e13, 1e14, 1e15, 1e16, 1e17, 1e18};
+    constexpr double kRcp10[19] = {1e-0,  1e-1,  1e-2,  1e-3,  1e-4,  1e-5,  1e-6,  1e-7,  1e-8, 1e-9,
+                                   1e-10, 1e-11, 1e-12, 1e-13, 1e-14, 1e-15, 1e-16, 1e-17, 1e-18};
+    return {kPow10[e], kRcp10[e]};
+}
 // A Float2Int integer (two's complement in 64 bits) as the bits of the
 // float64 (double)d / div: IEEE conversion and division, round to nearest.
-ZF_DEV uint64_t f2i_value(uint64_t d, double div) {
-    const double v = double(int64_t(d)) / div;
-    return uint64_t(__double_as_longlong(v));
+// The quotient a rcp is off by less than two units in the last place; one
+// residual correction brings it within one, and a second one from there is
+// the correctly rounded quotient, since rcp is the double nearest 1 / div
+// (Markstein, IBM J. Res. Dev. 34, 1990) and nothing here comes near the
+// ends of the exponent range.  Five multiply-adds against the general
+// division's scaling, reciprocal, refinement and fix-up: 0.4 us of a lone
+// block's 8.2, nothing of a large column's.
+ZF_DEV uint64_t f2i_value(uint64_t d, F2iScale c) {
+    const double a = __builtin_fma(double(int32_t(uint32_t(d >> 32))), 4294967296.0, double(uint32_t(d)));
+    double q = a * c.rcp;
+    q = __builtin_fma(__builtin_fma(-c.div, q, a), c.rcp, q);
+    q = __builtin_fma(__builtin_fma(-c.div, q, a), c.rcp, q);
+    return uint64_t(__double_as_longlong(q));
 }
 
 // The NW packed words starting at word k0 (NW <= 5, known per width);
@@ -300,60 +321,116 @@ ZF_DEV uint64_t yfield64(const Win &v, uint32_t sh) {
     }
 }
 
+// The NW packed words (NW <= 5, known per width) from byte `off` of a block's
+// payload, through its bounds-checked view: dwords past its end are zero.
+template <uint32_t NW>
+ZF_DEV Win load_view(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    Win v{0, 0, 0, 0, 0};
+    if constexpr (NW >= 4) {
+        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, int(off), 0, 0);
+        v.w0 = q.x; v.w1 = q.y; v.w2 = q.z; v.w3 = q.w;
+        if constexpr (NW == 5) v.w4 = __builtin_amdgcn_raw_buffer_load_b32(rs, int(off + 16), 0, 0);
+    } else if constexpr (NW == 3) {
+        const u32x3 q = __builtin_amdgcn_raw_buffer_load_b96(rs, int(off), 0, 0);
+        v.w0 = q.x; v.w1 = q.y; v.w2 = q.z;
+    } else if constexpr (NW == 2) {
+        const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(rs, int(off), 0, 0);
+        v.w0 = q.x; v.w1 = q.y;
+    } else if constexpr (NW == 1) {
+        v.w0 = __builtin_amdgcn_raw_buffer_load_b32(rs, int(off), 0, 0);
+    }
+    return v;
+}
+
+// The exceptions of a Float2Int block, as its steps need them: lane l holds
+// the bits of values [32 l, 32 l + 32), set where a value is an exception, and
+// the number of exceptions before them; the records are in order of their
+// values.
+struct F2iExc {
+    uint32_t n = 0, bits = 0, before = 0;
+    __amdgpu_buffer_rsrc_t recs;
+};
+
 // Decode one block of nv values, width W known at compile time.  A lane owns
 // 16 output bytes per step; the packed words of UNR steps are loaded before
-// any is used, so each wave keeps UNR x 1 KiB of output's loads in flight.
+// any is used, so each wave keeps UNR x 1 KiB of output's loads in flight.  A
+// step's 64 lanes take a whole number of words, so a lane's words lie the same
+// distance apart from step to step and its first bit at the same place in
+// them.  Words, output and dictionary are bounds-checked views (dwords past a
+// view's end read as zero and are not written), so that no lane branches: the
+// block's last lanes, a partial block and an output off the 16-byte grid take
+// the same instructions.  Against branches around each step's loads and
+// stores: 30,000 int64 of 24 bits 10.1 -> 6.3 us, 16.8 M 37.6 -> 31.2; 16.8 M
+// int32 of 20 bits 23.0 -> 20.4; 300,000 CHAR(16) 14.7 -> 7.2, 8 M 31.2 -> 27.0.
 // F2I: the 64-bit values are Float2Int integers, written as the float64
-// (double)int64(value) / div.
-// LDS: the dictionary was copied into this wave's LDS (dict points there).
+// (double)int64(value) / scale.div.
+// LDS: the dictionary was copied into this wave's LDS (dict).
 template <int ES, bool DICT, uint32_t UNR, uint32_t W, bool F2I = false, bool LDS = false>
-ZF_DEV void fp_block(const uint32_t *words, uint64_t nwords, uint64_t ref, uint32_t nv,
-                     uint8_t *ob, bool vec, const uint8_t *dict, uint32_t dict_count, bool &bad,
-                     double div = 1.0) {
+ZF_DEV void fp_block(__amdgpu_buffer_rsrc_t rs_words, uint64_t ref, uint32_t nv, __amdgpu_buffer_rsrc_t rs_out,
+                     __amdgpu_buffer_rsrc_t rs_dict, const uint8_t *dict, uint32_t dict_count, bool &bad,
+                     F2iScale scale, const F2iExc &exc) {
     constexpr uint32_t VPL = 16 / ES;
     constexpr uint32_t NW = (31 + VPL * W + 31) / 32;  // words a lane may need
-    const uint32_t lane = lane_id();
+    uint32_t lane = lane_id();
+    asm volatile("" : "+v"(lane));  // (every width's offsets, hoisted out of the block loop, would be kept at once)
     const uint32_t steps = (nv + 64 * VPL - 1) / (64 * VPL);
-    const ZF_GLOBAL uint8_t *gd = gp(dict);
+    const uint32_t bit = lane * VPL * W, sh = bit & 31u, off = (bit >> 5) * 4;
+    // a code past the dictionary reads entry 0 (LDS) or past the view, is
+    // written as zero, and is reported where it belongs to a value
+    auto lookup = [&](uint32_t v, uint32_t code, bool &ok) {
+        ok = code < dict_count;
+        bad |= v < nv && !ok;
+        return LDS ? (ok ? ES * code : 0u) : (ok ? ES * code : 0x7FFFFFF0u);
+    };
     for (uint32_t g = 0; g < steps; g += UNR) {
         Win wv[UNR];
 #pragma unroll
-        for (uint32_t u = 0; u < UNR; u++) {
-            const uint32_t v0 = ((g + u) * 64 + lane) * VPL;
-            if (v0 < nv) wv[u] = load_words<NW>(words, (uint64_t(v0) * W) >> 5, nwords);
+        for (uint32_t u = 0; u < UNR; u++) wv[u] = load_view<NW>(rs_words, off + (g + u) * (8 * VPL * W));
+        // F2I: the bits of the exceptions among this lane's values, merged
+        // before the store (8-byte stores over lines already on their way out
+        // cost a read of each line: 16.8 M doubles, one in eight an exception,
+        // 73 -> 43 us)
+        u32x2 ex[F2I ? UNR : 1][2];
+        uint32_t two[F2I ? UNR : 1];
+        if constexpr (F2I) {
+#pragma unroll
+            for (uint32_t u = 0; u < UNR; u++) two[u] = 0;
+            if (exc.n) {
+#pragma unroll
+                for (uint32_t u = 0; u < UNR; u++) {
+                    const int src = int(4 * (4 * (g + u) + (lane >> 4)));
+                    const uint32_t b = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(exc.bits)));
+                    const uint32_t before = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(exc.before)));
+                    const uint32_t at = 2 * (lane & 15u);
+                    two[u] = (b >> at) & 3u;
+                    const uint32_t r = before + uint32_t(__popc(b & ((1u << at) - 1u)));
+                    ex[u][0] = __builtin_amdgcn_raw_buffer_load_b64(
+                        exc.recs, int(two[u] & 1u ? 16 * r + 8 : 0x7FFFFFF0u), 0, 0);
+                    ex[u][1] = __builtin_amdgcn_raw_buffer_load_b64(
+                        exc.recs, int(two[u] & 2u ? 16 * (r + (two[u] & 1u)) + 8 : 0x7FFFFFF0u), 0, 0);
+                }
+            }
         }
 #pragma unroll
         for (uint32_t u = 0; u < UNR; u++) {
             const uint32_t v0 = ((g + u) * 64 + lane) * VPL;
-            if (v0 >= nv) continue;
-            const uint32_t sh = uint32_t((uint64_t(v0) * W) & 31u);
+            u32x4 q;
             if constexpr (ES == 4) {
-                uint32_t f[4] = {yfield32<W, 0>(wv[u], sh), yfield32<W, 1>(wv[u], sh),
-                                 yfield32<W, 2>(wv[u], sh), yfield32<W, 3>(wv[u], sh)};
-                uint32_t v[4];
+                const uint32_t f[4] = {yfield32<W, 0>(wv[u], sh), yfield32<W, 1>(wv[u], sh),
+                                       yfield32<W, 2>(wv[u], sh), yfield32<W, 3>(wv[u], sh)};
 #pragma unroll
                 for (uint32_t i = 0; i < 4; i++) {
-                    if constexpr (DICT && LDS) {
-                        const uint32_t code = uint32_t(ref) + f[i];
-                        const bool in = v0 + i < nv, ok = code < dict_count;
-                        bad |= in && !ok;
-                        const uint32_t x = *reinterpret_cast<const uint32_t *>(dict + 4 * (ok ? code : 0u));
-                        v[i] = (in && ok) ? x : 0u;
-                    } else if constexpr (DICT) {
-                        const uint32_t code = uint32_t(ref) + f[i];
-                        const bool in = v0 + i < nv, ok = code < dict_count;
-                        bad |= in && !ok;
-                        v[i] = (in && ok) ? *reinterpret_cast<const ZF_GLOBAL uint32_t *>(gd + 4ull * code) : 0u;
-                    } else {
-                        v[i] = uint32_t(ref) + f[i];
+                    q[i] = uint32_t(ref) + f[i];
+                    if constexpr (DICT) {
+                        bool ok;
+                        const uint32_t at = lookup(v0 + i, q[i], ok);
+                        if constexpr (LDS) {
+                            const uint32_t x = *reinterpret_cast<const uint32_t *>(dict + at);
+                            q[i] = ok ? x : 0u;
+                        } else {
+                            q[i] = __builtin_amdgcn_raw_buffer_load_b32(rs_dict, int(at), 0, 0);
+                        }
                     }
-                }
-                if (vec && v0 + 4 <= nv) {
-                    st16_nt(ob + 4ull * v0, v[0], v[1], v[2], v[3]);
-                } else {
-#pragma unroll
-                    for (uint32_t i = 0; i < 4; i++)
-                        if (v0 + i < nv) st4(ob + 4ull * (v0 + i), v[i]);
                 }
             } else if constexpr (ES == 8) {
                 uint64_t v[2];
@@ -361,55 +438,42 @@ ZF_DEV void fp_block(const uint32_t *words, uint64_t nwords, uint64_t ref, uint3
                     const uint32_t f[2] = {yfield32<W, 0>(wv[u], sh), yfield32<W, 1>(wv[u], sh)};
 #pragma unroll
                     for (uint32_t i = 0; i < 2; i++) {
-                        const uint32_t code = uint32_t(ref) + f[i];
-                        const bool in = v0 + i < nv, ok = code < dict_count;
-                        bad |= in && !ok;
+                        bool ok;
+                        const uint32_t at = lookup(v0 + i, uint32_t(ref) + f[i], ok);
                         if constexpr (LDS) {
-                            const uint64_t x = *reinterpret_cast<const uint64_t *>(dict + 8 * (ok ? code : 0u));
-                            v[i] = (in && ok) ? x : 0ull;
+                            const uint64_t x = *reinterpret_cast<const uint64_t *>(dict + at);
+                            v[i] = ok ? x : 0ull;
                         } else {
-                            v[i] = (in && ok) ? *reinterpret_cast<const ZF_GLOBAL uint64_t *>(gd + 8ull * code) : 0ull;
+                            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rs_dict, int(at), 0, 0);
+                            v[i] = uint64_t(x.x) | (uint64_t(x.y) << 32);
                         }
                     }
                 } else {
                     v[0] = ref + yfield64<W, 0>(wv[u], sh);
                     v[1] = ref + yfield64<W, 1>(wv[u], sh);
                     if constexpr (F2I) {
-                        v[0] = f2i_value(v[0], div);
-                        v[1] = f2i_value(v[1], div);
+#pragma unroll
+                        for (uint32_t i = 0; i < 2; i++) {
+                            v[i] = f2i_value(v[i], scale);
+                            if (two[u] & (1u << i)) v[i] = uint64_t(ex[u][i].x) | (uint64_t(ex[u][i].y) << 32);
+                        }
                     }
                 }
-                if (vec && v0 + 2 <= nv) {
-                    st16_nt(ob + 8ull * v0, uint32_t(v[0]), uint32_t(v[0] >> 32), uint32_t(v[1]),
-                            uint32_t(v[1] >> 32));
-                } else {
-#pragma unroll
-                    for (uint32_t i = 0; i < 2; i++)
-                        if (v0 + i < nv) {
-                            st4(ob + 8ull * (v0 + i), uint32_t(v[i]));
-                            st4(ob + 8ull * (v0 + i) + 4, uint32_t(v[i] >> 32));
-                        }
-                }
+                q = u32x4{uint32_t(v[0]), uint32_t(v[0] >> 32), uint32_t(v[1]), uint32_t(v[1] >> 32)};
             } else {  // ES == 16: dictionary of CHAR(16)
-                const uint32_t code = uint32_t(ref) + yfield32<W, 0>(wv[u], sh);
-                const bool ok = code < dict_count;
-                bad |= !ok;
-                u32x4 e = {0, 0, 0, 0};
+                bool ok;
+                const uint32_t at = lookup(v0, uint32_t(ref) + yfield32<W, 0>(wv[u], sh), ok);
                 if constexpr (LDS) {
-                    const u32x4 x = *reinterpret_cast<const u32x4 *>(dict + 16 * (ok ? code : 0u));
-                    e = ok ? x : e;
-                } else if (ok) {
-                    e = *reinterpret_cast<const ZF_GLOBAL u32x4 *>(gd + 16ull * code);
-                }
-                if (vec) {
-                    st16_nt(ob + 16ull * v0, e.x, e.y, e.z, e.w);
+                    const u32x4 x = *reinterpret_cast<const u32x4 *>(dict + at), zero = {0, 0, 0, 0};
+                    q = ok ? x : zero;
                 } else {
-                    st4(ob + 16ull * v0, e.x);
-                    st4(ob + 16ull * v0 + 4, e.y);
-                    st4(ob + 16ull * v0 + 8, e.z);
-                    st4(ob + 16ull * v0 + 12, e.w);
+                    q = __builtin_amdgcn_raw_buffer_load_b128(rs_dict, int(at), 0, 0);
                 }
             }
+            __builtin_amdgcn_raw_buffer_store_b128(q, rs_out, int(ES * v0), 0, kNonTemporal);
+            // (the quotients of one step at a time: interleaved, those of
+            // eight spill)
+            if constexpr (F2I) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
@@ -432,7 +496,7 @@ ZF_DEV uint64_t yfield_rt(uint32_t y0, uint32_t y1, uint32_t y2, uint32_t y3, ui
 template <int ES, bool DICT, bool F2I = false>
 ZF_DEV void fp_block_rt(uint32_t w, const uint32_t *words, uint64_t nwords, uint64_t ref, uint32_t nv,
                         uint8_t *ob, bool vec, const uint8_t *dict, uint32_t dict_count, bool &bad,
-                        double div = 1.0) {
+                        F2iScale scale = {}) {
     constexpr uint32_t VPL = 16 / ES;
     const uint32_t lane = lane_id();
     const ZF_GLOBAL uint8_t *gd = gp(dict);
@@ -467,7 +531,7 @@ ZF_DEV void fp_block_rt(uint32_t w, const uint32_t *words, uint64_t nwords, uint
                 }
             } else {
                 v[i] = ref + f;
-                if constexpr (F2I) v[i] = f2i_value(v[i], div);
+                if constexpr (F2I) v[i] = f2i_value(v[i], scale);
             }
         }
         if constexpr (ES == 4) {
@@ -490,16 +554,21 @@ ZF_DEV void fp_block_rt(uint32_t w, const uint32_t *words, uint64_t nwords, uint
 
 // Uniform dispatch on the block's width to its specialised decoder.
 template <int ES, bool DICT, uint32_t UNR, uint32_t W, uint32_t WMAX, bool F2I = false, bool LDS = false>
-ZF_DEV void fp_dispatch(uint32_t w, const uint32_t *words, uint64_t nwords, uint64_t ref, uint32_t nv,
-                        uint8_t *ob, bool vec, const uint8_t *dict, uint32_t dict_count, bool &bad,
-                        double div = 1.0) {
+ZF_DEV void fp_dispatch(uint32_t w, __amdgpu_buffer_rsrc_t rs_words, uint64_t ref, uint32_t nv,
+                        __amdgpu_buffer_rsrc_t rs_out, __amdgpu_buffer_rsrc_t rs_dict, const uint8_t *dict,
+                        uint32_t dict_count, bool &bad, F2iScale scale = {}, const F2iExc &exc = {}) {
     if constexpr (W <= WMAX) {
         if (w == W)
-            fp_block<ES, DICT, UNR, W, F2I, LDS>(words, nwords, ref, nv, ob, vec, dict, dict_count, bad, div);
+            fp_block<ES, DICT, UNR, W, F2I, LDS>(rs_words, ref, nv, rs_out, rs_dict, dict, dict_count, bad, scale,
+                                                 exc);
         else
-            fp_dispatch<ES, DICT, UNR, W + 1, WMAX, F2I, LDS>(w, words, nwords, ref, nv, ob, vec, dict, dict_count,
-                                                            bad, div);
+            fp_dispatch<ES, DICT, UNR, W + 1, WMAX, F2I, LDS>(w, rs_words, ref, nv, rs_out, rs_dict, dict,
+                                                            dict_count, bad, scale, exc);
     }
+}
+// A bounds-checked view of `bytes` bytes at p (the same on every lane).
+ZF_DEV __amdgpu_buffer_rsrc_t view(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(const_cast<void *>(p)), 0, int(first32(bytes)), 0x00020000);
 }
 
 // One wave decodes blocks [t.a, t.a + t.b) of a FOR_BP or DICT_BP chunk.
@@ -532,8 +601,7 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
             // 16 bytes per lane, through a view of the dictionary (a read past
             // it gives zeros)
             const uint32_t nbytes = ck.dict_count * ES;
-            const __amdgpu_buffer_rsrc_t rs =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(uniform_ptr(dict)), 0, int(nbytes), 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs = view(dict, nbytes);
             for (uint32_t k = lane_id(); 16 * k < nbytes; k += 64)
                 *reinterpret_cast<u32x4 *>(lds + 16 * k) = __builtin_amdgcn_raw_buffer_load_b128(rs, int(16 * k), 0, 0);
             wave_fence();
@@ -553,29 +621,34 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
         }
         const uint32_t *words = reinterpret_cast<const uint32_t *>(s + poff);
         uint8_t *ob = out + uint64_t(j0) * ES;
-        const bool vec = (reinterpret_cast<uintptr_t>(ob) & 15u) == 0;
-        if constexpr (MAXUNR == 0)
+        // (a dictionary of 2 GiB or more is past a view's offsets)
+        if (MAXUNR == 0 || (DICT && uint64_t(ck.dict_count) * ES > 0x7FFFFFF0u)) {
+            const bool vec = (reinterpret_cast<uintptr_t>(ob) & 15u) == 0;
             fp_block_rt<ES, DICT>(first32(w), words, nwords, ref, nv, ob, vec, dict, ck.dict_count, bad);
-        else if (DICT && in_lds)
-            fp_dispatch<ES, DICT, UNR, 0, BITS, false, true>(first32(w), words, nwords, ref, nv, ob, vec, lds,
-                                                             ck.dict_count, bad);
-        else
-            fp_dispatch<ES, DICT, UNR, 0, BITS>(first32(w), words, nwords, ref, nv, ob, vec, dict,
-                                                ck.dict_count, bad);
+        } else if constexpr (MAXUNR > 0) {
+            const __amdgpu_buffer_rsrc_t rw = view(words, uint32_t(4 * nwords)), ro = view(ob, nv * ES);
+            if (DICT && in_lds)
+                fp_dispatch<ES, DICT, UNR, 0, BITS, false, true>(first32(w), rw, ref, nv, ro, ro, lds, ck.dict_count,
+                                                                 bad);
+            else
+                fp_dispatch<ES, DICT, UNR, 0, BITS>(first32(w), rw, ref, nv, ro,
+                                                    DICT ? view(dict, ck.dict_count * ES) : ro, nullptr,
+                                                    ck.dict_count, bad);
+        }
     }
     if (any(bad)) flag(A.err, ERR_CORRUPT);
 }
 
 // One wave decodes blocks [t.a, t.a + t.b) of a Float2Int + bit-packing
 // chunk: the FOR + bit-packing unpack of the block's integers, each written
-// as (double)d / 10^e (fused: no intermediate integer array), then the
-// block's exceptions, stored raw over their slots by the same wave.
+// as (double)d / 10^e (fused: no intermediate integer array), with the
+// block's exceptions, stored raw, in their places.  lds: this wave's 64
+// dwords (unused by the runtime-width variant, whose exceptions are written
+// over their slots by the same wave).
 template <uint32_t MAXUNR>
-ZF_DEV void unit_f2i(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) {
+ZF_DEV void unit_f2i(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *lds) {
     constexpr uint32_t STEPS = kForBlock / 128;  // lane-steps per block (2 values each)
     constexpr uint32_t UNR = STEPS < MAXUNR ? STEPS : (MAXUNR ? MAXUNR : 1);
-    constexpr double kPow10[19] = {1e0,  1e1,  1e2,  1e3,  1e4,  1e5,  1e6,  1e7,  1e8, 1e9,
-                                   1e10, 1e11, 1e12, 1e13, 1e14, 1e15, 1e16, 1e17, 1e18};
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
     const uint32_t nb = (n + kForBlock - 1) / kForBlock;
@@ -600,24 +673,52 @@ ZF_DEV void unit_f2i(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) {
         }
         const uint32_t *words = reinterpret_cast<const uint32_t *>(s + poff);
         uint8_t *ob = out + uint64_t(j0) * 8;
-        const bool vec = (reinterpret_cast<uintptr_t>(ob) & 15u) == 0;
-        const double div = kPow10[first32(e)];
-        if constexpr (MAXUNR == 0)
-            fp_block_rt<8, false, true>(first32(w), words, nwords, ref, nv, ob, vec, nullptr, 0, bad, div);
-        else
-            fp_dispatch<8, false, UNR, 0, 64, true>(first32(w), words, nwords, ref, nv, ob, vec, nullptr, 0,
-                                                  bad, div);
-        // exceptions (issued after the block's stores by the same wave, so
-        // they land last)
-        for (uint32_t i = lane; i < nx; i += 64) {
+        const F2iScale scale = f2i_scale(first32(e));
+        // exception i's value: inside the block, after exception i - 1's
+        auto slot = [&](uint32_t i, bool &ok) {
             const uint8_t *r = s + xoff + 16ull * i;
             const uint32_t j = ld32u(r);
-            const bool ok = j < nv && (i == 0 || j > ld32u(r - 16));
+            ok = j < nv && (i == 0 || j > ld32u(r - 16));
             bad |= !ok;
-            if (ok) {
-                const u32x2 q = {ld32u(r + 8), ld32u(r + 12)};
-                __builtin_nontemporal_store(q, gp(reinterpret_cast<u32x2 *>(ob + 8ull * j)));
+            return j;
+        };
+        if constexpr (MAXUNR == 0) {
+            const bool vec = (reinterpret_cast<uintptr_t>(ob) & 15u) == 0;
+            fp_block_rt<8, false, true>(first32(w), words, nwords, ref, nv, ob, vec, nullptr, 0, bad, scale);
+            // exceptions (issued after the block's stores by the same wave,
+            // so they land last)
+            for (uint32_t i = lane; i < nx; i += 64) {
+                bool ok;
+                const uint32_t j = slot(i, ok);
+                if (ok) {
+                    const uint8_t *r = s + xoff + 16ull * i;
+                    const u32x2 q = {ld32u(r + 8), ld32u(r + 12)};
+                    __builtin_nontemporal_store(q, gp(reinterpret_cast<u32x2 *>(ob + 8ull * j)));
+                }
             }
+        } else {
+            F2iExc exc;
+            exc.n = first32(nx);
+            exc.recs = view(s + xoff, 16 * nx);
+            if (exc.n) {
+                lds[lane] = 0;
+                wave_fence();
+                for (uint32_t i = lane; i < nx; i += 64) {
+                    bool ok;
+                    const uint32_t j = slot(i, ok);
+                    if (ok)
+                        __hip_atomic_fetch_or(lds + (j >> 5), 1u << (j & 31u), __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                wave_fence();
+                exc.bits = lds[lane];
+                const uint32_t c = uint32_t(__popc(exc.bits));
+                exc.before = scan_add32(c) - c;
+                wave_fence();
+            }
+            const __amdgpu_buffer_rsrc_t ro = view(ob, nv * 8);
+            fp_dispatch<8, false, UNR, 0, 64, true>(first32(w), view(words, uint32_t(4 * nwords)), ref, nv, ro, ro,
+                                                  nullptr, 0, bad, scale, exc);
         }
     }
     if (any(bad)) flag(A.err, ERR_CORRUPT);
@@ -2081,7 +2182,7 @@ ZF_DEV void run_unit(const LaunchArgs &A, uint32_t kind, uint32_t u, uint32_t *l
     switch (kind) {
     case K_PLAIN: unit_plain(A, t, ck); break;
     case K_FOR32: unit_fp<4, false, UNR>(A, t, ck); break;
-    case K_F2I: unit_f2i<UNR>(A, t, ck); break;
+    case K_F2I: unit_f2i<UNR>(A, t, ck, lz_row); break;
     case K_FOR64: unit_fp<8, false, UNR>(A, t, ck); break;
     case K_DICT32: unit_fp<4, true, UNR>(A, t, ck); break;
     case K_DICT64: unit_fp<8, true, UNR>(A, t, ck); break;
@@ -2134,7 +2235,8 @@ __global__ __launch_bounds__(1024) void k_decode_kind(LaunchArgs A) {
     } else if constexpr (KIND == K_FOR64) {
         unit_fp<8, false, 8>(A, t, ck);
     } else if constexpr (KIND == K_F2I) {
-        unit_f2i<8>(A, t, ck);
+        extern __shared__ __attribute__((aligned(16))) uint8_t dict_lds[];
+        unit_f2i<4>(A, t, ck, reinterpret_cast<uint32_t *>(dict_lds) + (threadIdx.x / 64) * 64);
     } else if constexpr (KIND == K_DICT32 || KIND == K_DICT64 || KIND == K_DICT128) {
         // each wave's dictionary copy, kDictLds bytes of dynamic shared memory
         extern __shared__ __attribute__((aligned(16))) uint8_t dict_lds[];
@@ -2198,7 +2300,8 @@ ZF_KIND_LAUNCHERS(ZF_DECLARE_LAUNCHER)
     void NAME(const LaunchArgs &A, uint32_t waves, hipStream_t st) {                               \
         const uint32_t n = A.kind_begin[KIND + 1] - A.kind_begin[KIND];                            \
         if (!n) return;                                                                            \
-        const uint32_t lds = (KIND == K_DICT32 || KIND == K_DICT64 || KIND == K_DICT128) ? waves * kDictLds : 0; \
+        const uint32_t lds = (KIND == K_DICT32 || KIND == K_DICT64 || KIND == K_DICT128) ? waves * kDictLds          \
+                             : KIND == K_F2I ? waves * 256 : 0;                                    \
         hipLaunchKernelGGL(k_decode_kind<KIND>, dim3((n + waves - 1) / waves), dim3(64 * waves), lds, st, A); \
     }
 

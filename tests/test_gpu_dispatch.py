@@ -3,6 +3,7 @@ oracle's decode of the same bytes."""
 import numpy as np
 import pytest
 
+import oracle.zfo as zo
 from paper_2602_08190_amd import datagen as g
 from paper_2602_08190_amd import zf
 
@@ -83,3 +84,58 @@ def test_smallest_units(d):
     for slot in (1 << 14, 1 << 20):
         outs, _ = decode_staged(cols, slot_bytes=slot)
         check(cols, outs, xs)
+
+
+def f2i_bits(cols, outs, xs):
+    for c, o, x in zip(cols, outs, xs):
+        assert np.array_equal(o.view(np.uint64), x.view(np.uint64))
+        assert np.array_equal(zo.decode(c.bytes()).view(np.uint64), x.view(np.uint64))
+
+
+@pytest.mark.parametrize("n", [1, 127, 2048, 2049, 7001])
+def test_f2i_exceptions_in_place(n):
+    # exceptions nowhere, everywhere, at the ends of blocks and steps, in pairs
+    r = g.rng(n)
+    i = np.arange(n)
+    cols, xs = [], []
+    for where in (i < 0, i >= 0, i % 2 == 1, i % 128 == 127, (i % 2048 == 0) | (i % 2048 == 2047) | (i == n - 1),
+                  r.random(n) < 0.1, (i // 3) % 5 == 2):
+        x = r.integers(1, 10 ** 6, size=n) / 100.0
+        x = np.where(where, r.random(n) * 1e-3, x)
+        xs.append(x)
+        cols.append(zf.Column.compress(x, zf.F2I_BP, chunk_elems=[n] if n < 5000 else [2047, 2051, n - 4098]))
+    f2i_bits(cols, decode_image(cols), xs)
+    f2i_bits(cols, decode_image(cols, persistent=True), xs)
+
+
+@pytest.mark.parametrize("bits", [20, 53, 61])
+def test_f2i_quotients_of_every_exponent(bits):
+    # d / 10^e for every e, d up to 2^bits in magnitude, exact powers among
+    # them: the same doubles as IEEE division
+    cols, xs = [], []
+    for e in range(19):
+        r = g.rng(100 * bits + e)
+        d = r.integers(-(1 << bits), 1 << bits, size=3 * 2048)
+        d[:64] = [s * (1 << min(k, bits)) for k in range(32) for s in (1, -1)]
+        x = d.astype(np.float64) / np.float64(10 ** e)
+        xs.append(x)
+        cols.append(zf.Column.compress(x, zf.F2I_BP))
+    f2i_bits(cols, decode_image(cols), xs)
+    f2i_bits(cols, decode_image(cols, persistent=True), xs)
+
+
+@pytest.mark.parametrize("n_entries", [1, 3, 255, 256, 257, 1024, 1025])
+def test_dict_views(n_entries):
+    # dictionaries up to 4 KiB (gathered from LDS) and past it, whose sizes
+    # end inside a 16-byte load; chunks off the output's 16-byte grid
+    r = g.rng(n_entries)
+    cols, xs = [], []
+    for kind in ("i4", "i8", "c16"):
+        n = 2 * 2048 + 333
+        d = g.fixed16_dictionary(n_entries, 7) if kind == "c16" else \
+            np.arange(n_entries).astype(kind) * 1000003 - 5
+        code = np.concatenate([np.arange(n_entries), r.integers(0, n_entries, size=n)])
+        xs.append(d[code])
+        m = len(code)
+        cols.append(zf.Column.compress(xs[-1], zf.DICT_BP, chunk_elems=[2049, 1, 2, m - 2052]))
+    check(cols, decode_image(cols), xs)
