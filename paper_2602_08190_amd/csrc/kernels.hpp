@@ -14,11 +14,10 @@
 //    l, an exclusive wave scan of the counts gives each run's output offset
 //    (the paper's presum, fused), an inclusive wave scan of the unpacked
 //    deltas gives the run values.  Output is written in windows of 64 lanes x
-//    16 bytes: every run starting in a window marks its start in an LDS slot,
-//    a wave max-scan carries the latest run over the window and each lane
-//    fetches its run's value with a cross-lane permute, so a window costs the
-//    same whatever its run count.  Units are balanced by output count on the
-//    host.
+//    16 bytes: every run's start is a bit in a map of 2048 elements, an
+//    element's run the count of bits up to it, and each lane fetches its run's
+//    value with a cross-lane permute, so a window costs the same whatever its
+//    run count.  Units are balanced by output count on the host.
 //  String dictionary (Sec. 5.3) is a Group-Parallel expansion too: a wave
 //    takes groups of 64 tokens, scans their lengths for output offsets and
 //    gathers each token's bytes into a per-wave LDS staging buffer that is
@@ -728,23 +727,10 @@ ZF_DEV void unit_f2i(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
 // One wave writes elements [t.b, t.c) of an RLE_DELTA_BP / DELTA_BP chunk,
 // starting at group t.a.  Per group of 64 runs, lane j holds run j: an
 // exclusive scan of the run lengths gives the run starts (the paper's presum,
-// fused), an inclusive scan of dmin + field gives the run values.  The next
-// group's record, run lengths and packed words are loaded while this one is
-// expanded.  Expansion goes by windows of 64 lanes x 16 bytes of output:
-// each run starting in the window writes its index into an LDS slot at its
-// start, a wave scan carries the latest index over the window, and each lane
-// takes its values with cross-lane permutes — no per-run loop.  slot: this
-// wave's 256 dwords.
-// One group's record and this lane's run length and packed words.  For
-// DeltaStride, w/doff/w0..w2 are the gap field's and wd/dw0..dw2 the stride
-// field's.
-template <class T>
-struct RleGroup {
-    uint32_t goff, w, doff, next_off, r, w0, w1, w2;
-    uint32_t wd, dw0, dw1, dw2;
-    T base, dmin, gmin;
-    bool ok;
-};
+// fused), an inclusive scan of dmin + field gives the run values.  The records
+// of the unit's groups are read at once, one per lane, so that a group's run
+// lengths and packed words are on their way while the group before it is
+// expanded, and nothing waits for a record in between.
 
 // Field of width w at bit `bit` of a packed stream, from the three words
 // starting at word bit / 32.
@@ -758,90 +744,130 @@ ZF_DEV U field_of(uint32_t w0, uint32_t w1, uint32_t w2, uint64_t bit, uint32_t 
         return (sh ? ((lo >> sh) | (uint64_t(w2) << (64 - sh))) : lo) & mask64(w);
     }
 }
+// The words of field j (width w) of a packed stream at byte `at` of a stream
+// s that ends at byte `end` (zeros past it): two or three dwords in one load.
+template <class U>
+ZF_DEV u32x3 field_words(const uint8_t *s, uint32_t at, uint32_t end, uint32_t j, uint32_t w) {
+    const __amdgpu_buffer_rsrc_t rs = view(s, end);
+    const uint32_t o = at + 4 * ((j * w) >> 5);
+    if constexpr (sizeof(U) == 8) return __builtin_amdgcn_raw_buffer_load_b96(rs, int(o), 0, 0);
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, int(o), 0, 0);
+    return u32x3{v.x, v.y, 0u};
+}
+template <class U>
+ZF_DEV U field_from(u32x3 v, uint32_t j, uint32_t w) {
+    return field_of<U>(v.x, v.y, v.z, j * w, w);
+}
+
+// Inclusive sums of a group's run lengths and their total: 32-bit scans unless
+// a length (of a corrupt stream, or a very long run) could make them wrap.
+ZF_DEV uint32_t scan_lengths(uint32_t r, uint32_t last, uint64_t &total) {
+    if (any(r >> 26)) {
+        const uint64_t incl = scan_add64(r);
+        total = rl64(incl, last);
+        return uint32_t(incl);
+    }
+    const uint32_t incl = scan_add32(r);
+    total = rl32(incl, last);
+    return incl;
+}
+
+// How a run's values follow from its own: the same value throughout, a
+// progression with the run's stride, a progression with one stride for all.
+enum class Run { kConst, kStride, kOneStride };
 
 // Expansion of one group of up to 64 runs into out[a, bnd): lane j holds run
-// j (act), its output range [start_abs, end_abs) and its value: v for RLE
-// (DS = false), v + dstr * p at element p for progressions (DS = true).
-// Output goes by windows of 64 lanes x 16 bytes: each run starting in the
-// window writes its index into an LDS slot at its start, a wave scan carries
-// the latest index over the window, and each lane takes its values with
-// cross-lane permutes — no per-run loop.  slot: this wave's 256 dwords.
-template <class U, bool DS>
-ZF_DEV void expand_runs(U *out, uint32_t a, uint32_t bnd, bool act, uint32_t start_abs, uint32_t end_abs, U v,
-                        U dstr, uint32_t *slot) {
-    constexpr uint32_t BITS = sizeof(U) * 8;
+// j (act), which starts at start_abs, and its value: v (kConst), or v + dstr *
+// p at element p.  Output goes by spans of 2048 elements.  Every run that
+// starts in the span sets its bit in a map of 64 words, one per lane, so that
+// an element's run is the runs that start before the span, plus the set bits
+// up to the element: a count per word from one scan, and the bits of the
+// element's own word.  Each lane then takes 16 bytes of output, its values
+// fetched from their runs with cross-lane permutes: no per-run loop, and the
+// same work whatever the run lengths.  map: this wave's 64 dwords.
+// 33.6 M int32 in runs of 8 (3): 45.6 (73) us with a slot per element and a
+// carry from window to window, 37.0 (58) us so; order keys 58.6 and 46.1.
+template <class U, Run RUN>
+ZF_DEV void expand_runs(U *out, uint32_t a, uint32_t bnd, bool act, uint32_t start_abs, U v, U dstr, uint32_t *map) {
+    constexpr uint32_t R = 16 / sizeof(U), WIN = 64 * R, SPAN = 2048;
+    if (a >= bnd) return;
     const uint32_t lane = lane_id();
-    // R outputs per lane per window (16 bytes: one aligned store when whole)
-    constexpr uint32_t R = 16 / sizeof(U), SPAN = 64 * R;
-    if (a < bnd) {
-        // window grid aligned so that out + W0 + R * lane is 16-byte aligned
-        // (signed: the first window may start before element 0)
-        const int32_t mis = int32_t((reinterpret_cast<uintptr_t>(out + a) & 15u) / sizeof(U));
-        const int32_t ia = int32_t(a), ib = int32_t(bnd);
-        // 1 + index of the run holding a (a run index, plus one, marks a start)
-        uint32_t carry = 1 + uint32_t(__popcll(__ballot(act && end_abs <= a)));
-        for (int32_t W0 = ia - mis; W0 < ib; W0 += int32_t(SPAN)) {
-#pragma unroll
-            for (uint32_t i = 0; i < R; i++) slot[64 * i + lane] = 0;
-            wave_fence();
-            // element W0 + R l + i has slot 64 i + l
-            const uint32_t rel = start_abs - uint32_t(W0);
-            if (act && rel < SPAN && start_abs >= a) slot[64 * (rel % R) + rel / R] = lane + 1;
-            wave_fence();
-            uint32_t m[R], last = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < R; i++) {
-                m[i] = slot[64 * i + lane];
-                last = m[i] ? m[i] : last;
-            }
-            uint32_t cur1 = last_nonzero_below(last, carry);
+    auto fetch = [&](int src, U x) -> U {
+        if constexpr (sizeof(U) == 4) {
+            return uint32_t(__builtin_amdgcn_ds_bpermute(src, int(x)));
+        } else {
+            const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(x))));
+            const uint32_t hi = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(x >> 32))));
+            return uint64_t(lo) | (uint64_t(hi) << 32);
+        }
+    };
+    // spans on the output's 16-byte grid (signed: the first may start before
+    // element 0)
+    const int32_t mis = int32_t((reinterpret_cast<uintptr_t>(out + a) & 15u) / sizeof(U));
+    const int32_t ia = int32_t(a), ib = int32_t(bnd);
+    const uint32_t sh = (R * lane) & 31u, upto = (2u << sh) - 1u;  // bits up to the lane's first element's
+    for (int32_t S = ia - mis; S < ib; S += int32_t(SPAN)) {
+        map[lane] = 0;
+        wave_fence();
+        const uint32_t rel = start_abs - uint32_t(S);
+        if (act && rel < SPAN)
+            __hip_atomic_fetch_or(map + (rel >> 5), 1u << (rel & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        wave_fence();
+        const uint32_t bits = map[lane], c = uint32_t(__popc(bits));
+        // runs that start before this lane's word, less one
+        const uint32_t before = scan_add32(c) - c + uint32_t(__popcll(__ballot(act && int32_t(start_abs) < S))) - 1u;
+        wave_fence();
+        const int32_t E = min(S + int32_t(SPAN), ib);
+        for (int32_t W = S; W < E; W += int32_t(WIN)) {
+            const int word = int(uint32_t(W - S) / 8 + ((R * lane) >> 5) * 4);  // (4 x the word's lane)
+            const uint32_t b = uint32_t(__builtin_amdgcn_ds_bpermute(word, int(bits)));
+            uint32_t run = uint32_t(__builtin_amdgcn_ds_bpermute(word, int(before))) + uint32_t(__popc(b & upto));
+            const int32_t p = W + int32_t(R * lane);
             U val[R];
 #pragma unroll
             for (uint32_t i = 0; i < R; i++) {
-                cur1 = m[i] ? m[i] : cur1;
-                const int src = int((cur1 - 1) * 4);
-                if constexpr (BITS == 32) {
-                    val[i] = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(v)));
-                } else {
-                    const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(v))));
-                    const uint32_t hi = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(v >> 32))));
-                    val[i] = uint64_t(lo) | (uint64_t(hi) << 32);
-                }
-                if constexpr (DS) {
-                    // plus stride * element index
-                    U dd;
-                    if constexpr (BITS == 32) {
-                        dd = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(dstr)));
-                    } else {
-                        const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(dstr))));
-                        const uint32_t hi =
-                            uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(dstr >> 32))));
-                        dd = uint64_t(lo) | (uint64_t(hi) << 32);
-                    }
-                    val[i] = U(val[i] + dd * U(uint32_t(W0 + int32_t(R * lane + i))));
-                }
+                if (i) run += (b >> (sh + i)) & 1u;
+                const int src = int(run * 4);
+                val[i] = fetch(src, v);
+                if constexpr (RUN == Run::kStride) val[i] = U(val[i] + fetch(src, dstr) * U(uint32_t(p + int32_t(i))));
+                if constexpr (RUN == Run::kOneStride) val[i] = U(val[i] + dstr * U(uint32_t(p + int32_t(i))));
             }
-            const int32_t p = W0 + int32_t(R * lane);
             if (p >= ia && p + int32_t(R) <= ib) {
                 u32x4 q;
-                if constexpr (BITS == 32) q = u32x4{val[0], val[1], val[2], val[3]};
+                if constexpr (sizeof(U) == 4) q = u32x4{val[0], val[1], val[2], val[3]};
                 else q = u32x4{uint32_t(val[0]), uint32_t(val[0] >> 32), uint32_t(val[1]), uint32_t(val[1] >> 32)};
                 __builtin_nontemporal_store(q, gp(reinterpret_cast<u32x4 *>(out + p)));
             } else {
 #pragma unroll
                 for (int32_t i = 0; i < int32_t(R); i++)
-                    if (p + i >= ia && p + i < ib) out[p + i] = val[i];
+                    if (p + i >= ia && p + i < ib) gp(out)[p + i] = val[i];
             }
-            wave_fence();
         }
     }
 }
+
+// A window of up to 64 group records, one per lane (the record's first 16
+// bytes, and its next 16 where it has them): groups g0 on, the last group's
+// again past the end.
+struct RecWindow {
+    uint32_t g0;
+    u32x4 a, b;
+    template <uint32_t BYTES>
+    ZF_DEV void load(const uint8_t *recs, uint32_t g, uint32_t ng) {
+        g0 = g;
+        const u32x4 *r = reinterpret_cast<const u32x4 *>(recs + uint64_t(BYTES) * min(g + lane_id(), ng - 1));
+        a = gp(r)[0];
+        if constexpr (BYTES == 32) b = gp(r)[1];
+    }
+    // groups g, g + 1 and g + 2 in the window
+    ZF_DEV bool has(uint32_t g) const { return g - g0 <= 61; }
+};
 
 // Group-Parallel decode of RLE_DELTA_BP / DELTA_BP (DS = false) and
 // DSTRIDE_BP (DS = true) chunks: one wave expands the groups that meet its
 // tile's element range [t.b, t.c), starting with group t.a.
 template <class T, bool DS>
-ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *slot) {
+ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *map) {
     using U = T;  // unsigned value type: uint32_t or uint64_t
     constexpr uint32_t BITS = sizeof(T) * 8;
     const uint8_t *s = A.comp + ck.comp_off;
@@ -852,7 +878,7 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    const uint32_t nr = ld32u(s), ng = ld32u(s + 4), roff = ld32u(s + 8);
+    const uint32_t nr = first32(ld32u(s)), ng = first32(ld32u(s + 4)), roff = first32(ld32u(s + 8));
     bool hdr_ok = ng == (uint64_t(nr) + kRleGroup - 1) / kRleGroup && 16ull + 32ull * ng <= clen;
     if (unit_runs) hdr_ok = hdr_ok && nr == n && roff == 0;
     else hdr_ok = hdr_ok && (roff & 3u) == 0 && roff >= 16ull + 32ull * ng && roff + 4ull * nr <= clen;
@@ -861,55 +887,82 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    const uint32_t *runs = reinterpret_cast<const uint32_t *>(s + roff);
-    // record, run length and packed words of group g (bounds checked before
-    // any load that depends on the record)
-    auto load = [&](uint32_t g, RleGroup<U> &G) {
-        const uint8_t *rec = s + 16 + 32ull * g;
-        G.goff = ld32u(rec);
-        G.base = U(ld64u(rec + 16));
-        G.dmin = U(ld64u(rec + 24));
-        G.next_off = (g + 1 < ng) ? ld32u(rec + 32) : n;
-        const uint32_t cnt = min(kRleGroup, nr - g * kRleGroup);
-        uint64_t nwords, dwords = 0;
+    const __amdgpu_buffer_rsrc_t rs_runs = view(s + roff, unit_runs ? 0u : 4 * nr);
+    RecWindow rec;
+    rec.load<32>(s + 16, t.a, ng);
+    // A group's record {out_off, w, doff, 0, base, dmin} (DeltaStride:
+    // {out_off, poff, widths, 0, base, dmin}, the fields at poff + 8), checked
+    // before anything is read through it, and this lane's run length and
+    // packed words.
+    struct Group {
+        uint32_t goff, next_off, cnt, w, wd, r;
+        u32x3 f, d;  // field words: deltas (gaps), strides
+        U base, dmin, gmin;
+        bool ok;
+    };
+    auto load = [&](uint32_t g, Group &G) {
+        const uint32_t i = g - rec.g0;
+        G.goff = rl32(rec.a.x, i);
+        G.next_off = g + 1 < ng ? rl32(rec.a.x, i + 1) : n;
+        G.base = U(uint64_t(rl32(rec.b.x, i)) | (uint64_t(rl32(rec.b.y, i)) << 32));
+        G.dmin = U(uint64_t(rl32(rec.b.z, i)) | (uint64_t(rl32(rec.b.w, i)) << 32));
+        G.cnt = min(kRleGroup, nr - g * kRleGroup);
+        const uint32_t r1 = rl32(rec.a.y, i), r2 = rl32(rec.a.z, i);
+        uint32_t at;
         if constexpr (DS) {
-            const uint32_t poff = ld32u(rec + 4), widths = ld32u(rec + 8);
-            G.w = widths & 0xFFu;
-            G.wd = (widths >> 8) & 0xFFu;
-            G.doff = poff + 8;
-            nwords = (uint64_t(cnt - 1) * min(G.w, 64u) + 31) / 32;
-            dwords = (uint64_t(cnt) * min(G.wd, 64u) + 31) / 32;
-            G.ok = G.w <= BITS && G.wd <= BITS && (widths >> 16) == 0 && (poff & 7u) == 0 &&
-                   poff + 8 + 4 * (nwords + dwords) <= clen && G.next_off <= n;
-            G.gmin = G.ok ? U(ld64u(s + poff)) : U(0);
+            G.w = r2 & 0xFFu;
+            G.wd = (r2 >> 8) & 0xFFu;
+            at = r1 + 8;
         } else {
-            G.w = ld32u(rec + 4);
-            G.doff = ld32u(rec + 8);
-            nwords = (uint64_t(cnt - 1) * min(G.w, 64u) + 31) / 32;
-            G.ok = G.w <= BITS && (G.doff & 3u) == 0 && G.doff + 4 * nwords <= clen && G.next_off <= n;
+            G.w = r1;
+            G.wd = 0;
+            at = r2;
         }
-        const bool act = lane < cnt;
-        G.r = act ? (unit_runs ? 1u : runs[uint64_t(g) * kRleGroup + lane]) : 0u;
-        G.w0 = G.w1 = G.w2 = 0;
-        const uint32_t *words = reinterpret_cast<const uint32_t *>(s + G.doff);
-        if (G.ok && lane >= 1 && act) {
-            const uint64_t k = (uint64_t(lane - 1) * G.w) >> 5;
-            G.w0 = k < nwords ? words[k] : 0u;
-            G.w1 = k + 1 < nwords ? words[k + 1] : 0u;
-            if constexpr (BITS == 64) G.w2 = k + 2 < nwords ? words[k + 2] : 0u;
-        }
+        const uint32_t nwords = ((G.cnt - 1) * min(G.w, 64u) + 31) / 32, dwords = (G.cnt * min(G.wd, 64u) + 31) / 32;
+        const uint64_t end = uint64_t(at) + 4 * nwords;
+        if constexpr (DS)
+            G.ok = G.w <= BITS && G.wd <= BITS && (r2 >> 16) == 0 && (r1 & 7u) == 0 && r1 <= clen &&
+                   end + 4 * dwords <= clen && G.next_off <= n;
+        else
+            G.ok = G.w <= BITS && (at & 3u) == 0 && end <= clen && G.next_off <= n;
+        G.r = 1;
+        G.f = G.d = u32x3{0u, 0u, 0u};
+        G.gmin = 0;
+        if (!G.ok) return;
+        if (!unit_runs) G.r = __builtin_amdgcn_raw_buffer_load_b32(rs_runs, int(4 * (g * kRleGroup + lane)), 0, 0);
+        // (lane j's delta is field j - 1; lane 0 takes field 0 and leaves it)
+        G.f = field_words<U>(s, at, uint32_t(end), lane ? lane - 1 : 0u, G.w);
         if constexpr (DS) {
-            G.dw0 = G.dw1 = G.dw2 = 0;
-            if (G.ok && act) {
-                const uint32_t *dw = words + nwords;
-                const uint64_t k = (uint64_t(lane) * G.wd) >> 5;
-                G.dw0 = k < dwords ? dw[k] : 0u;
-                G.dw1 = k + 1 < dwords ? dw[k + 1] : 0u;
-                if constexpr (BITS == 64) G.dw2 = k + 2 < dwords ? dw[k + 2] : 0u;
-            }
+            G.d = field_words<U>(s, uint32_t(end), uint32_t(end) + 4 * dwords, lane, G.wd);
+            G.gmin = U(ld64u(s + r1));
         }
     };
-    RleGroup<U> cur, nxt;
+    if (!DS && unit_runs) {
+        // Runs of one (DELTA_BP): lane j holds element j of its group, whose
+        // values go straight out, four groups' words asked for at once.
+        // 33.6 M int32: 169 us as runs, 65 us so.
+        constexpr uint32_t NG = 4;
+        for (uint32_t g = t.a;; g += NG) {
+            if (g - rec.g0 > 63 - NG) rec.load<32>(s + 16, g, ng);
+            Group G[NG];
+#pragma unroll
+            for (uint32_t k = 0; k < NG; k++) load(min(g + k, ng - 1), G[k]);
+#pragma unroll
+            for (uint32_t k = 0; k < NG; k++) {
+                const Group &q = G[k];
+                if (g + k >= ng || !q.ok || (g + k == t.a && q.goff > e0) || q.goff + q.cnt != q.next_off) {
+                    flag(A.err, ERR_CORRUPT);
+                    return;
+                }
+                const U delta = lane ? U(q.dmin + field_from<U>(q.f, lane - 1, q.w)) : q.base;
+                const U v = scan_addT<U>(lane < q.cnt ? delta : U(0));
+                const uint32_t p = q.goff + lane;
+                if (lane < q.cnt && p >= e0 && p < e1) __builtin_nontemporal_store(v, gp(out + p));
+                if (q.next_off >= e1) return;
+            }
+        }
+    }
+    Group cur, nxt;
     load(t.a, cur);
     for (uint32_t g = t.a;; g++) {
         if (!cur.ok || (g == t.a && cur.goff > e0)) {
@@ -922,44 +975,40 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
                 flag(A.err, ERR_CORRUPT);
                 return;
             }
+            if (!rec.has(g)) rec.load<32>(s + 16, g, ng);
             load(g + 1, nxt);  // in flight while this group is expanded
         }
-        const uint32_t cnt = min(kRleGroup, nr - g * kRleGroup);
         // run lengths -> output offsets (exclusive scan = presum)
-        const bool act = lane < cnt;
-        const uint32_t r = cur.r;
-        const uint64_t incl = scan_add64(r);
-        const uint64_t total = rl64(incl, cnt - 1);
+        const bool act = lane < cur.cnt;
+        const uint32_t r = act ? cur.r : 0u;
+        uint64_t total;
+        const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
         if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
-        const uint32_t end_abs = cur.goff + uint32_t(incl);  // end of run `lane`
-        const uint32_t start_abs = end_abs - r;
+        const uint32_t start_abs = cur.goff + incl - r;  // start of run `lane`
         // RLE: run values are base, then base + prefix sums of (dmin + field).
         // DeltaStride: run j writes c_j + d_j * p at element p, with stride
         // d_j = dmin + field, start s_j = s_{j-1} + d_{j-1} r_{j-1} + gap_j
         // (gap_j = gmin + field, s_0 = base) and c_j = s_j - d_j * start_j.
+        const U field = field_from<U>(cur.f, lane - 1, cur.w);  // (lane 0's is not used)
         U v, dstr = 0;
         if constexpr (DS) {
-            dstr = act ? U(cur.dmin + field_of<U>(cur.dw0, cur.dw1, cur.dw2, uint64_t(lane) * cur.wd, cur.wd))
-                       : U(0);
+            dstr = act ? U(cur.dmin + field_from<U>(cur.d, lane, cur.wd)) : U(0);
             // start_j = base + sum_{k<j} stride_k count_k + sum_{k<=j} gap_k:
             // an exclusive and an inclusive wave scan, no cross-lane reads
             const U f = act ? U(dstr * U(r)) : U(0);
-            const U gap = (act && lane >= 1)
-                              ? U(cur.gmin + field_of<U>(cur.w0, cur.w1, cur.w2, uint64_t(lane - 1) * cur.w, cur.w))
-                              : U(0);
+            const U gap = act && lane >= 1 ? U(cur.gmin + field) : U(0);
             const U F = scan_addT<U>(f), Gs = scan_addT<U>(gap);
             const U st = U(cur.base + (F - f) + Gs);
             v = U(st - dstr * U(start_abs));
         } else {
-            U delta = cur.base;
-            if (lane >= 1 && act)
-                delta = U(cur.dmin + field_of<U>(cur.w0, cur.w1, cur.w2, uint64_t(lane - 1) * cur.w, cur.w));
+            const U delta = lane ? U(cur.dmin + field) : cur.base;
             v = scan_addT<U>(act ? delta : U(0));
         }
-        expand_runs<U, DS>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs, end_abs, v, dstr, slot);
+        expand_runs<U, DS ? Run::kStride : Run::kConst>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs,
+                                                         v, dstr, map);
         if (!more) return;
         cur = nxt;
     }
@@ -972,29 +1021,13 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
 // of D is the progression P_j + V_j (p - a_j + 1) over its positions p, P_j
 // the sum before it (the group's base plus an exclusive wave scan of V L).
 // The second expands the DeltaStride runs (start S_k from the scratch area,
-// count C_k bit-packed per group, the chunk's stride d) into the output.
-
-// Field j (width w <= 32) of packed words at p, from two bounds-checked loads.
-ZF_DEV uint32_t field32_at(const uint8_t *p, uint64_t nwords, uint32_t j, uint32_t w) {
-    const uint64_t bit = uint64_t(j) * w, k = bit >> 5;
-    const uint32_t *words = reinterpret_cast<const uint32_t *>(p);
-    const uint32_t w0 = k < nwords ? words[k] : 0u, w1 = k + 1 < nwords ? words[k + 1] : 0u;
-    return field_of<uint32_t>(w0, w1, 0u, bit, w);
-}
-template <class U>
-ZF_DEV U fieldU_at(const uint8_t *p, uint64_t nwords, uint32_t j, uint32_t w) {
-    const uint64_t bit = uint64_t(j) * w, k = bit >> 5;
-    const uint32_t *words = reinterpret_cast<const uint32_t *>(p);
-    const uint32_t w0 = k < nwords ? words[k] : 0u, w1 = k + 1 < nwords ? words[k + 1] : 0u;
-    uint32_t w2 = 0;
-    if constexpr (sizeof(U) == 8) w2 = k + 2 < nwords ? words[k + 2] : 0u;
-    return field_of<U>(w0, w1, w2, bit, w);
-}
+// count C_k bit-packed per group, the chunk's stride d) into the output.  Both
+// read their groups' records and the next group's words ahead, as unit_rle.
 
 // First stage: S[t.b, t.c) of a chunk (ck.n_elems = R starts, written at
 // out_tab[kScratchCol] + ck.out_off), starting with D's group t.a.
 template <class U>
-ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *slot) {
+ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *map) {
     constexpr uint32_t BITS = sizeof(U) * 8;
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t R = ck.n_elems, clen = ck.comp_len, lane = lane_id();
@@ -1003,53 +1036,82 @@ ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    const uint32_t Q = ld32u(s + 8), ngA = ld32u(s + 12);
+    const uint32_t Q = first32(ld32u(s + 8)), ngA = first32(ld32u(s + 12));
     const uint32_t e0 = t.b, e1 = t.c;
-    if (ld32u(s) != R || Q == 0 || Q > R || ngA != (uint64_t(Q) + 63) / 64 || 32ull + 32ull * ngA > clen ||
+    if (first32(ld32u(s)) != R || Q == 0 || Q > R || ngA != (uint64_t(Q) + 63) / 64 || 32ull + 32ull * ngA > clen ||
         e1 > R || e0 >= e1 || t.a >= ngA) {
         flag(A.err, ERR_CORRUPT);
         return;
     }
+    RecWindow rec;
+    rec.load<32>(s + 32, t.a, ngA);
+    // record {out_off, poff, widths, lmin, base, vmin}
+    struct Group {
+        uint32_t goff, next_off, cnt, wv, wl, lmin;
+        u32x3 v, l;
+        U base, vmin;
+        bool ok;
+    };
+    auto load = [&](uint32_t g, Group &G) {
+        const uint32_t i = g - rec.g0;
+        G.goff = rl32(rec.a.x, i);
+        G.next_off = g + 1 < ngA ? rl32(rec.a.x, i + 1) : R;
+        const uint32_t poff = rl32(rec.a.y, i), widths = rl32(rec.a.z, i);
+        G.lmin = rl32(rec.a.w, i);
+        G.base = U(uint64_t(rl32(rec.b.x, i)) | (uint64_t(rl32(rec.b.y, i)) << 32));
+        G.vmin = U(uint64_t(rl32(rec.b.z, i)) | (uint64_t(rl32(rec.b.w, i)) << 32));
+        G.cnt = min(64u, Q - 64 * g);
+        G.wv = widths & 0xFFu;
+        G.wl = (widths >> 8) & 0xFFu;
+        const uint32_t vw = (G.cnt * min(G.wv, 64u) + 31) / 32, lw = (G.cnt * min(G.wl, 64u) + 31) / 32;
+        G.ok = G.wv <= BITS && G.wl <= 32 && (widths >> 16) == 0 && (poff & 3u) == 0 &&
+               uint64_t(poff) + 4 * (vw + lw) <= clen && G.next_off <= R;
+        G.v = G.l = u32x3{0u, 0u, 0u};
+        if (!G.ok) return;
+        G.v = field_words<U>(s, poff, poff + 4 * vw, lane, G.wv);
+        G.l = field_words<uint32_t>(s, poff + 4 * vw, poff + 4 * (vw + lw), lane, G.wl);
+    };
+    Group cur, nxt;
+    load(t.a, cur);
     for (uint32_t g = t.a;; g++) {
-        const uint8_t *rec = s + 32 + 32ull * g;
-        const uint32_t goff = ld32u(rec), poff = ld32u(rec + 4), widths = ld32u(rec + 8), lmin = ld32u(rec + 12);
-        const U base = U(ld64u(rec + 16)), vmin = U(ld64u(rec + 24));
-        const uint32_t next_off = g + 1 < ngA ? ld32u(rec + 32) : R;
-        const uint32_t cnt = min(64u, Q - 64 * g), wv = widths & 0xFFu, wl = (widths >> 8) & 0xFFu;
-        const uint64_t vw = (uint64_t(cnt) * min(wv, 64u) + 31) / 32, lw = (uint64_t(cnt) * min(wl, 64u) + 31) / 32;
-        if (wv > BITS || wl > 32 || (widths >> 16) != 0 || (poff & 3u) != 0 || poff + 4 * (vw + lw) > clen ||
-            next_off > R || (g == t.a && goff > e0)) {
+        if (!cur.ok || (g == t.a && cur.goff > e0)) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
-        const bool act = lane < cnt;
-        const U vj = act ? U(vmin + fieldU_at<U>(s + poff, vw, lane, wv)) : U(0);
-        const uint32_t r = act ? lmin + field32_at(s + poff + 4 * vw, lw, lane, wl) : 0u;
-        const uint64_t incl = scan_add64(r);
-        const uint64_t total = rl64(incl, cnt - 1);
-        if (any(act && r == 0) || uint64_t(goff) + total != next_off) {
+        const bool more = cur.next_off < e1;
+        if (more) {
+            if (g + 1 >= ngA) {
+                flag(A.err, ERR_CORRUPT);
+                return;
+            }
+            if (!rec.has(g)) rec.load<32>(s + 32, g, ngA);
+            load(g + 1, nxt);
+        }
+        const bool act = lane < cur.cnt;
+        const U vj = act ? U(cur.vmin + field_from<U>(cur.v, lane, cur.wv)) : U(0);
+        const uint32_t r = act ? cur.lmin + field_from<uint32_t>(cur.l, lane, cur.wl) : 0u;
+        uint64_t total;
+        const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
+        if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
-        const uint32_t end_abs = goff + uint32_t(incl), start_abs = end_abs - r;
+        const uint32_t start_abs = cur.goff + incl - r;
         // run j: value P_j + V_j at its first position, then + V_j per position
         const U f = act ? U(vj * U(r)) : U(0);
         const U F = scan_addT<U>(f);
-        const U first = U(base + (F - f) + vj);
+        const U first = U(cur.base + (F - f) + vj);
         const U c = U(first - vj * U(start_abs));
-        expand_runs<U, true>(out, max(e0, goff), min(e1, next_off), act, start_abs, end_abs, c, vj, slot);
-        if (next_off >= e1) return;
-        if (g + 1 >= ngA) {
-            flag(A.err, ERR_CORRUPT);
-            return;
-        }
+        expand_runs<U, Run::kStride>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs, c, vj, map);
+        if (!more) return;
+        cur = nxt;
     }
 }
 
 // Second stage: output elements [t.b, t.c) of a chunk, starting with run
 // group t.a; the starts S are in the scratch area at ck.aux_off.
 template <class U>
-ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *slot) {
+ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *map) {
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
     U *out = reinterpret_cast<U *>(A.out_tab[ck.col] + ck.out_off);
@@ -1058,41 +1120,67 @@ ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, u
         flag(A.err, ERR_CORRUPT);
         return;
     }
-    const uint32_t R = ld32u(s), ngB = ld32u(s + 4), ngA = ld32u(s + 12), b_off = ld32u(s + 24);
-    const U d = U(ld64u(s + 16));
+    const uint32_t R = first32(ld32u(s)), ngB = first32(ld32u(s + 4)), ngA = first32(ld32u(s + 12)),
+                   b_off = first32(ld32u(s + 24));
+    const U d = U(uint64_t(first32(ld32u(s + 16))) | (uint64_t(first32(ld32u(s + 20))) << 32));
     const uint32_t e0 = t.b, e1 = t.c;
     if (R == 0 || R > n || ngB != (uint64_t(R) + 63) / 64 || b_off != 32ull + 32ull * ngA ||
         uint64_t(b_off) + 16ull * ngB > clen || e1 > n || e0 >= e1 || t.a >= ngB) {
         flag(A.err, ERR_CORRUPT);
         return;
     }
+    RecWindow rec;
+    rec.load<16>(s + b_off, t.a, ngB);
+    // record {out_off, poff, wc, cmin}
+    struct Group {
+        uint32_t goff, next_off, cnt, wc, cmin;
+        u32x3 c;
+        U st;
+        bool ok;
+    };
+    auto load = [&](uint32_t g, Group &G) {
+        const uint32_t i = g - rec.g0;
+        G.goff = rl32(rec.a.x, i);
+        G.next_off = g + 1 < ngB ? rl32(rec.a.x, i + 1) : n;
+        const uint32_t poff = rl32(rec.a.y, i);
+        G.wc = rl32(rec.a.z, i);
+        G.cmin = rl32(rec.a.w, i);
+        G.cnt = min(64u, R - 64 * g);
+        const uint32_t cw = (G.cnt * min(G.wc, 64u) + 31) / 32;
+        G.ok = G.wc <= 32 && (poff & 3u) == 0 && uint64_t(poff) + 4 * cw <= clen && G.next_off <= n;
+        G.c = u32x3{0u, 0u, 0u};
+        G.st = lane < G.cnt ? gp(S)[64ull * g + lane] : U(0);
+        if (G.ok) G.c = field_words<uint32_t>(s, poff, poff + 4 * cw, lane, G.wc);
+    };
+    Group cur, nxt;
+    load(t.a, cur);
     for (uint32_t g = t.a;; g++) {
-        const uint8_t *rec = s + b_off + 16ull * g;
-        const uint32_t goff = ld32u(rec), poff = ld32u(rec + 4), wc = ld32u(rec + 8), cmin = ld32u(rec + 12);
-        const uint32_t next_off = g + 1 < ngB ? ld32u(rec + 16) : n;
-        const uint32_t cnt = min(64u, R - 64 * g);
-        const uint64_t cw = (uint64_t(cnt) * min(wc, 64u) + 31) / 32;
-        if (wc > 32 || (poff & 3u) != 0 || poff + 4 * cw > clen || next_off > n || (g == t.a && goff > e0)) {
+        if (!cur.ok || (g == t.a && cur.goff > e0)) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
-        const bool act = lane < cnt;
-        const uint32_t r = act ? cmin + field32_at(s + poff, cw, lane, wc) : 0u;
-        const U st = act ? S[64ull * g + lane] : U(0);
-        const uint64_t incl = scan_add64(r);
-        const uint64_t total = rl64(incl, cnt - 1);
-        if (any(act && r == 0) || uint64_t(goff) + total != next_off) {
+        const bool more = cur.next_off < e1;
+        if (more) {
+            if (g + 1 >= ngB) {
+                flag(A.err, ERR_CORRUPT);
+                return;
+            }
+            if (!rec.has(g)) rec.load<16>(s + b_off, g, ngB);
+            load(g + 1, nxt);
+        }
+        const bool act = lane < cur.cnt;
+        const uint32_t r = act ? cur.cmin + field_from<uint32_t>(cur.c, lane, cur.wc) : 0u;
+        uint64_t total;
+        const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
+        if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
-        const uint32_t end_abs = goff + uint32_t(incl), start_abs = end_abs - r;
-        const U c = U(st - d * U(start_abs));
-        expand_runs<U, true>(out, max(e0, goff), min(e1, next_off), act, start_abs, end_abs, c, d, slot);
-        if (next_off >= e1) return;
-        if (g + 1 >= ngB) {
-            flag(A.err, ERR_CORRUPT);
-            return;
-        }
+        const uint32_t start_abs = cur.goff + incl - r;
+        const U c = U(cur.st - d * U(start_abs));
+        expand_runs<U, Run::kOneStride>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs, c, d, map);
+        if (!more) return;
+        cur = nxt;
     }
 }
 
@@ -2175,7 +2263,7 @@ ZF_DEV void unit_plain(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) 
 template <uint32_t UNR>
 // lz_row: this wave's LDS scratch (max(kAnsLdsWords, kSdBufAlloc) dwords):
 // the LZ77 row, the ANS model and staging, the String-dictionary buffer or
-// the RLE window slots.
+// the RLE span's map.
 ZF_DEV void run_unit(const LaunchArgs &A, uint32_t kind, uint32_t u, uint32_t *lz_row) {
     const Tile t = A.tiles[u];
     const ChunkDesc ck = A.chunks[t.chunk];
@@ -2245,19 +2333,19 @@ __global__ __launch_bounds__(1024) void k_decode_kind(LaunchArgs A) {
         else if constexpr (KIND == K_DICT64) unit_fp<8, true, 8>(A, t, ck, lds);
         else unit_fp<16, true, 8>(A, t, ck, lds);
     } else if constexpr (KIND == K_RLE32) {
-        __shared__ uint32_t rle_slots[16][256];
-        if (ck.codec == C_DSTRIDE_BP) unit_rle<uint32_t, true>(A, t, ck, rle_slots[threadIdx.x / 64]);
-        else if (ck.codec == C_DSTREE_STARTS) unit_tree_starts<uint32_t>(A, t, ck, rle_slots[threadIdx.x / 64]);
-        else unit_rle<uint32_t, false>(A, t, ck, rle_slots[threadIdx.x / 64]);
+        __shared__ uint32_t rle_maps[16][64];
+        if (ck.codec == C_DSTRIDE_BP) unit_rle<uint32_t, true>(A, t, ck, rle_maps[threadIdx.x / 64]);
+        else if (ck.codec == C_DSTREE_STARTS) unit_tree_starts<uint32_t>(A, t, ck, rle_maps[threadIdx.x / 64]);
+        else unit_rle<uint32_t, false>(A, t, ck, rle_maps[threadIdx.x / 64]);
     } else if constexpr (KIND == K_RLE64) {
-        __shared__ uint32_t rle_slots[16][256];
-        if (ck.codec == C_DSTRIDE_BP) unit_rle<uint64_t, true>(A, t, ck, rle_slots[threadIdx.x / 64]);
-        else if (ck.codec == C_DSTREE_STARTS) unit_tree_starts<uint64_t>(A, t, ck, rle_slots[threadIdx.x / 64]);
-        else unit_rle<uint64_t, false>(A, t, ck, rle_slots[threadIdx.x / 64]);
+        __shared__ uint32_t rle_maps[16][64];
+        if (ck.codec == C_DSTRIDE_BP) unit_rle<uint64_t, true>(A, t, ck, rle_maps[threadIdx.x / 64]);
+        else if (ck.codec == C_DSTREE_STARTS) unit_tree_starts<uint64_t>(A, t, ck, rle_maps[threadIdx.x / 64]);
+        else unit_rle<uint64_t, false>(A, t, ck, rle_maps[threadIdx.x / 64]);
     } else if constexpr (KIND == K_TREE) {
-        __shared__ uint32_t rle_slots[16][256];
-        if (ck.dtype == D_I32) unit_tree<uint32_t>(A, t, ck, rle_slots[threadIdx.x / 64]);
-        else unit_tree<uint64_t>(A, t, ck, rle_slots[threadIdx.x / 64]);
+        __shared__ uint32_t rle_maps[16][64];
+        if (ck.dtype == D_I32) unit_tree<uint32_t>(A, t, ck, rle_maps[threadIdx.x / 64]);
+        else unit_tree<uint64_t>(A, t, ck, rle_maps[threadIdx.x / 64]);
     }
 }
 

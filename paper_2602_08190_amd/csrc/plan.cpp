@@ -198,11 +198,13 @@ struct KindLoad {
 // fastest on gigabytes; what a launch of less takes is the time of one unit as
 // long as its units do not fill the GPU, so a kind's unit shrinks until the
 // launch has 8,192 of them or more (32 waves on each of 256 compute units; 4,096
-// String-dictionary units, whose prologue is long), and a workgroup holds no
-// more waves than leaves two workgroups per compute unit.  Shapes the caller
-// set stay.  Units of 256 elements, 1,024 bytes of tokens, one block and 8 KiB
-// of plain copy are the smallest: smaller ones were no faster.  Measured, with
-// the cache's shape and this rule's:
+// for the group-parallel kinds, whose units begin with a longer prologue), and
+// a workgroup holds no more waves than leaves two workgroups per compute unit.
+// Shapes the caller set stay.  Units of 256 elements, 1,024 bytes of tokens,
+// one block and 8 KiB of plain copy are the smallest: smaller ones were no
+// faster.  The DSTREE output, which the cache does not hold, takes units of at
+// most 512 (33.6 M int64 keys 84 -> 71 us, int32 46 us with any).  Measured,
+// with the cache's shape and this rule's:
 //   String-dictionary, 1.5 MB 81 -> 10.5 us, 16 MiB 83 -> 20, 64 MiB 86 -> 46
 //   DSTREE output, 3 M keys 25 -> 10 us; RLE32, 300,000 dates 10.2 -> 7.0
 //   Float2Int, 300,000 doubles 36 -> 12.4 us; DICT128, 300,000 16.4 -> 13.6
@@ -224,8 +226,9 @@ static TileShape fit_tiles(TileShape t, const zf_plan_opts &o, const KindLoad &L
             if (!o.tiles[k].unit) t.unit[k] = std::min(t.unit[k], 16384u);
         }
         if (!o.tiles[k].unit) {
+            if (k == K_TREE) t.unit[k] = std::min(t.unit[k], 512u);
             const uint32_t least = k == K_PLAIN ? 8192u : sd ? 1024u : gp ? 256u : 1u;
-            uint64_t u = L.n[k] / ((sd ? 16u : 32u) * cus);
+            uint64_t u = L.n[k] / ((sd || gp ? 16u : 32u) * cus);
             u = pow2_floor(u);  // (as the cache's)
             if (u < t.unit[k]) t.unit[k] = uint32_t(std::clamp<uint64_t>(u, std::min(least, t.unit[k]), t.unit[k]));
         }

@@ -139,3 +139,27 @@ def test_dict_views(n_entries):
         m = len(code)
         cols.append(zf.Column.compress(xs[-1], zf.DICT_BP, chunk_elems=[2049, 1, 2, m - 2052]))
     check(cols, decode_image(cols), xs)
+
+
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("unit", [64, 2048, 2049, 8192])
+def test_spans_of_the_run_map(dtype, unit):
+    # runs that start, end and lie across the 2048-element spans of the run
+    # map, units of one span and around it, 64 groups' records and more in a
+    # unit, a run longer than 2^26, chunks off the output's 16-byte grid
+    r = g.rng(unit)
+    runs = [np.full(5, 2048), np.full(300, 1), np.full(3, 2047), np.full(7, 2049), np.full(65 * 64, 1),
+            r.integers(1, 5000, size=40), r.integers(1, 4, size=9000)]
+    x = g.column_from_runs(np.concatenate(runs).astype(np.int64), 3, dtype)
+    keys = g.orderkey_column(150_001, 4, dtype=dtype)
+    ce = lambda n: [1, 3, 5, n // 2, n - n // 2 - 9]  # noqa: E731
+    xs = [x, x, keys, g.key_column(60_007, 5, dtype=dtype), np.arange(70_001).astype(dtype) * 3]
+    codecs = [zf.RLE_DELTA_BP, zf.DELTA_BP, zf.DSTREE, zf.DSTRIDE_BP, zf.DELTA_BP]
+    cols = [zf.Column.compress(v, c, chunk_elems=ce(len(v))) for v, c in zip(xs, codecs)]
+    check(cols, decode_image(cols, tiles={"GP": dict(unit=unit)}), xs)
+    check(cols, decode_image(cols), xs)
+    if unit == 8192 and dtype == np.int32:
+        big = np.repeat(np.array([7, -3, 9], dtype), [(1 << 26) + 5, 3, 700])
+        col = zf.Column.compress(big, zf.RLE_DELTA_BP, chunk_elems=[len(big)])
+        out, = decode_image([col])
+        assert np.array_equal(out, big)
