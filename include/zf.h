@@ -274,7 +274,8 @@ typedef enum {
 /* Tile shape of one kind, the device geometry of Sec. 4 (<L,S,C>): `unit`
  * is the work of one wavefront (FP: 2048-value blocks; GP: output elements;
  * PLAIN: bytes; LZ77: output bytes per block of the copy step, 4, 8 or 16,
- * one chunk per wavefront; the persistent kernel always uses 4; SDICT:
+ * one chunk per wavefront; the persistent kernel always uses 4; with neither
+ * field set, launches of few chunks decode each in a workgroup's LDS; SDICT:
  * output bytes, in whole groups of 64 tokens),
  * `waves_per_block`
  * the wavefronts per workgroup (S/64; SDICT: at most 12, or 14 and 16, which

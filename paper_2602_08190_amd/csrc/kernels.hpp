@@ -1472,6 +1472,255 @@ ZF_DEV void unit_lz(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *row) {
     if (pos != plain || lp != nlit || ep != next) flag(A.err, ERR_CORRUPT);
 }
 
+// The same chunk decoded by a workgroup of W waves with the whole output in
+// LDS.  A chunk is a chain of batches, each copying from what the ones before
+// it wrote, so its time is the latency of a copy times its batches; from
+// memory that is the trip of every store and load, from LDS a tenth of it.
+// Wave w takes batch W g + w of each group of W batches: the waves parse side
+// by side (their batches' sizes meet in LDS), place all literals, then copy
+// their matches in turn, a barrier between two turns, while the next group's
+// tags, offsets and extension words are on their way.  A flat batch reads only
+// what earlier batches wrote and its own literals, so its lanes read all their
+// matches' dwords, then write them; the last dword of a match ends with it, so
+// no byte past it is written.  Matches of more than 36 bytes and those that
+// overlap themselves are copied by the whole wave one by one; a batch that is
+// not flat is replayed in order (one sequence by one).  The finished chunk is written once, in
+// aligned 16-byte stores.  LZ_FIGURES
+// lds: the waves' piece lists, 3 W + 1 dwords rounded up to 16 bytes, then the
+// output laid on its 16-byte grid and 16 bytes past it.
+constexpr uint32_t kLzPieces = 256;  // a wave's list of dword copies
+template <uint32_t W>
+constexpr uint32_t lz_head() { return 4 * kLzPieces * W + ((4 * (3 * W + 1) + 15) & ~15u); }
+template <uint32_t W>
+ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
+    const uint8_t *s = A.comp + ck.comp_off;
+    const uint32_t clen = ck.comp_len, lane = lane_id(), w = first32(threadIdx.x / 64);
+    const uint32_t es = ck.dtype == D_I32 ? 4 : ck.dtype == D_I64 ? 8 : ck.dtype == D_FIXED16 ? 16 : 1;
+    const uint32_t plain = ck.n_elems * es;
+    uint8_t *out = uniform_ptr(A.out_tab[ck.col] + ck.out_off);
+    if (clen < 16) {
+        flag(A.err, ERR_CORRUPT);
+        return;
+    }
+    const uint32_t nseq = first32(ld32u(s)), nlit = first32(ld32u(s + 4));
+    const uint32_t next = first32(ld32u(s + 8)), plen = first32(ld32u(s + 12));
+    if (plen != plain || plain > kLzMaxChunk || 16ull + 3ull * nseq + 2ull * next + nlit != uint64_t(clen)) {
+        flag(A.err, ERR_CORRUPT);
+        return;
+    }
+    const ZF_GLOBAL uint16_t *offs = gp(reinterpret_cast<const uint16_t *>(s + 16)), *ext = offs + nseq;
+    const ZF_GLOBAL uint8_t *tags = reinterpret_cast<const ZF_GLOBAL uint8_t *>(ext + next), *lits = tags + nseq;
+    uint32_t *list = reinterpret_cast<uint32_t *>(lds) + kLzPieces * w;
+    uint32_t *n_ext = reinterpret_cast<uint32_t *>(lds) + kLzPieces * W, *n_out = n_ext + W, *n_lit = n_ext + 2 * W,
+             *failed = n_ext + 3 * W;
+    const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(out) & 15u);
+    uint8_t *ob = lds + lz_head<W>() + mis;  // ob[p]: output byte p
+    if (threadIdx.x == 0) *failed = 0;
+    // sum of the waves' values below this one's (base) and of all (total)
+    auto share = [&](const uint32_t *v, uint32_t &base, uint32_t &total) {
+        const uint32_t x = v[lane & (W - 1)];
+        base = total = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < W; k++) {
+            const uint32_t y = rl32(x, k);
+            base += k < w ? y : 0u;
+            total += y;
+        }
+    };
+    // tag and offset of this lane's sequence of group g
+    uint32_t tag = 0, off = 0, ntag = 0, noff = 0;
+    auto fetch = [&](uint32_t g, uint32_t &t, uint32_t &o) {
+        const uint64_t i = (uint64_t(g) * W + w) * 64 + lane;
+        t = i < nseq ? tags[i] : 0u;
+        o = i < nseq ? offs[i] : 0u;
+    };
+    // the batch's count of extension words goes to the other waves; the
+    // lane's own number within the batch
+    auto count_ext = [&](uint32_t t) {
+        const uint64_t b7 = __ballot((t & 7u) == 7u), b31 = __ballot((t >> 3) == 31u);
+        if (lane == 0) n_ext[w] = uint32_t(__popcll(b7) + __popcll(b31));
+        return __builtin_amdgcn_mbcnt_hi(uint32_t(b7 >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(b7), 0u)) +
+               __builtin_amdgcn_mbcnt_hi(uint32_t(b31 >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(b31), 0u));
+    };
+    uint32_t pos = 0, lp = 0, ep = 0, x1 = 0, x2 = 0;
+    // extension words ep + 2 lane and ep + 2 lane + 1, loaded a group ahead;
+    // words past the window, where a group has many, are loaded when needed
+    uint32_t win = 0, win_at = 0;
+    auto fetch_win = [&]() {
+        const uint32_t e = ep + 2 * lane;
+        win_at = ep;
+        win = (e < next ? uint32_t(ext[e]) : 0u) | (e + 1 < next ? uint32_t(ext[e + 1]) << 16 : 0u);
+    };
+    // extension words of this lane's sequence, the k-th of its batch on
+    auto take_ext = [&](uint32_t t, uint32_t k) {
+        uint32_t base, total;
+        share(n_ext, base, total);
+        const uint32_t e = ep + base + k, e2 = e + ((t & 7u) == 7u), r = e - win_at, r2 = e2 - win_at;
+        const uint32_t y = uint32_t(__builtin_amdgcn_ds_bpermute(int(2 * r & ~3u), int(win)));
+        const uint32_t y2 = uint32_t(__builtin_amdgcn_ds_bpermute(int(2 * r2 & ~3u), int(win)));
+        const bool n1 = (t & 7u) == 7u, n2 = (t >> 3) == 31u;
+        x1 = n1 ? (r & 1u ? y >> 16 : y & 0xFFFFu) : 0u;
+        x2 = n2 ? (r2 & 1u ? y2 >> 16 : y2 & 0xFFFFu) : 0u;
+        if (any((n1 && r >= 128) || (n2 && r2 >= 128))) {
+            x1 = n1 && e < next ? ext[e] : 0u;
+            x2 = n2 && e2 < next ? ext[e2] : 0u;
+        }
+        ep += total;
+    };
+    // bytes [q, q + min(m, o)) to [d, d + m), over and over, all lanes
+    auto copy_long = [&](uint32_t d, uint32_t q, uint32_t m, uint32_t o) {
+        uint32_t r = lane, step = 64;
+        if (o < m) {
+            r = lane % o;
+            step = 64 % o;
+        }
+        for (uint32_t j = lane; j < m; j += 64) {
+            ob[d + j] = ob[q + r];
+            r += step;
+            if (o < m && r >= o) r -= o;
+        }
+        wave_fence();
+    };
+    fetch(0, tag, off);
+    fetch_win();
+    const uint32_t k0 = count_ext(tag);
+    __syncthreads();
+    take_ext(tag, k0);
+    fetch_win();
+    const uint32_t groups = (nseq + 64 * W - 1) / (64 * W);
+    fetch(1, ntag, noff);
+    for (uint32_t g = 0; g < groups; g++) {
+        const uint32_t lc = tag & 7u, mc = tag >> 3;
+        uint32_t ll = lc, ml = 0;
+        if (lc == 7u) ll = 7u + x1;
+        if (mc == 31u) ml = 34u + x2;
+        else if (mc) ml = mc + 3u;
+        const uint32_t len = ll + ml;
+        const uint32_t pincl = scan_add32(len), lincl = scan_add32(ll);
+        if (lane == 63) {
+            n_out[w] = pincl;
+            n_lit[w] = lincl;
+        }
+        __syncthreads();
+        uint32_t pb, pt, lb, lt;
+        share(n_out, pb, pt);
+        share(n_lit, lb, lt);
+        const uint32_t start = pos + pb;  // the batch's first output byte
+        const uint32_t P = start + pincl - len, LP = lp + lb + lincl - ll, D = P + ll, q0 = D - off;
+        const bool act = (uint64_t(g) * W + w) * 64 + lane < nseq;
+        const bool bad = act && (uint64_t(P) + len > plain || uint64_t(LP) + ll > nlit ||
+                                 (ml == 0 ? off != 0 : (off == 0 || off > D)));
+        if (any(bad)) {
+            if (lane == 0) *failed = 1;
+            ll = ml = 0;  // (nothing of the batch is copied)
+        }
+        // the next group's literals begin at lp + lt: their lines are asked for
+        const uint64_t l2 = uint64_t(lp) + lt + 4 * threadIdx.x;
+        const uint32_t ahead = l2 < nlit ? lits[l2] : 0u;
+        const bool flat = !any(ml != 0 && q0 + min(ml, off) > start && q0 < P);
+        // literals: up to 32 bytes by the lane, four at a time, the last four
+        // ending with the run; runs under four byte by byte
+        {
+            const uint32_t m = ll <= 32 ? ll : 0u;
+            if (any(m != 0)) {
+                uint32_t v[8];
+#pragma unroll
+                for (uint32_t i = 0; i < 8; i++) {
+                    v[i] = 0;
+                    if (any(m > 4 * i)) {
+                        const uint32_t o = LP + (m >= 4 ? min(4 * i, m - 4) : 0u);
+                        if (m > 4 * i && o + 4 <= nlit) __builtin_memcpy(&v[i], (const uint8_t *)(lits + o), 4);
+                    }
+                }
+                const bool edge = m && m < 4 && LP + 4 > nlit;  // (the array's last bytes)
+                if (any(edge) && edge)
+                    for (uint32_t k = 0; k < m; k++) v[0] |= uint32_t(lits[LP + k]) << (8 * k);
+                if (m && m < 4) {
+                    ob[P] = uint8_t(v[0]);
+                    if (m > 1) ob[P + 1] = uint8_t(v[0] >> 8);
+                    if (m > 2) ob[P + 2] = uint8_t(v[0] >> 16);
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < 8; i++)
+                    if (any(m >= 4 && m > 4 * i) && m >= 4 && m > 4 * i)
+                        __builtin_memcpy(ob + P + min(4 * i, m - 4), &v[i], 4);
+            }
+            for (uint64_t b = __ballot(ll > 32); b; b &= b - 1) {
+                const uint32_t k = uint32_t(__builtin_ctzll(b)), Pk = rl32(P, k), Lk = rl32(LP, k), lk = rl32(ll, k);
+                for (uint32_t j = lane; j < lk; j += 64) ob[Pk + j] = lits[Lk + j];
+            }
+        }
+        const uint32_t nk = count_ext(ntag);
+        __syncthreads();
+        if (*failed) {
+            flag(A.err, ERR_CORRUPT);
+            return;
+        }
+        take_ext(ntag, nk);
+        fetch_win();
+        uint32_t fetched_tag, fetched_off;
+        fetch(g + 2, fetched_tag, fetched_off);
+        // the batch's matches as a list of dword copies {from, to}, of which
+        // the lanes take equal shares
+        uint32_t m = flat && ml <= 36 && off >= ml ? ml : 0u;  // (at least 4 if any)
+        const uint32_t pincl2 = scan_add32((m + 3) >> 2), at = pincl2 - ((m + 3) >> 2);
+        const uint64_t fits = __ballot(pincl2 <= kLzPieces);  // (the first lanes)
+        if (pincl2 > kLzPieces) m = 0;
+        const uint32_t pieces = fits ? rl32(pincl2, uint32_t(__popcll(fits)) - 1) : 0u;
+#pragma unroll
+        for (uint32_t i = 0; i < 9; i++)
+            if (any(m > 4 * i)) {
+                const uint32_t o = min(4 * i, m - 4);
+                if (m > 4 * i) list[at + i] = (q0 + o) | ((D + o) << 16);
+            }
+        wave_fence();
+        uint32_t piece[kLzPieces / 64];
+#pragma unroll
+        for (uint32_t i = 0; i < kLzPieces / 64; i++) piece[i] = list[64 * i + lane];
+        // matches, batch after batch
+        const uint32_t turns = min(W, (nseq - 64 * W * g + 63) / 64);
+        for (uint32_t v = 0; v < turns; v++) {
+            if (v == w) {
+                uint32_t x[kLzPieces / 64];
+#pragma unroll
+                for (uint32_t i = 0; i < kLzPieces / 64; i++)
+                    if (64 * i < pieces && 64 * i + lane < pieces)
+                        __builtin_memcpy(&x[i], ob + (piece[i] & 0xFFFFu), 4);
+#pragma unroll
+                for (uint32_t i = 0; i < kLzPieces / 64; i++)
+                    if (64 * i < pieces && 64 * i + lane < pieces) __builtin_memcpy(ob + (piece[i] >> 16), &x[i], 4);
+                for (uint64_t b = __ballot(ml != 0 && m == 0); b; b &= b - 1) {
+                    const uint32_t k = uint32_t(__builtin_ctzll(b));
+                    copy_long(rl32(D, k), rl32(q0, k), rl32(ml, k), rl32(off, k));
+                }
+            }
+            __syncthreads();
+        }
+        asm volatile("" ::"v"(ahead));
+        pos += pt;
+        lp += lt;
+        tag = ntag;
+        off = noff;
+        ntag = fetched_tag;
+        noff = fetched_off;
+    }
+    if (pos != plain || lp != nlit || ep != next) {
+        flag(A.err, ERR_CORRUPT);
+        return;
+    }
+    const uint8_t *ib = lds + lz_head<W>();
+    for (uint32_t b = threadIdx.x; 16 * b < mis + plain; b += 64 * W) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(ib + 16 * b);
+        uint8_t *q = out - mis + 16 * b;
+        if (16 * b >= mis && 16 * b + 16 <= mis + plain) {
+            __builtin_nontemporal_store(v, gp(reinterpret_cast<u32x4 *>(q)));
+        } else {
+            for (uint32_t k = 0; k < 16; k++)
+                if (16 * b + k >= mis && 16 * b + k < mis + plain) gp(q)[k] = uint8_t(v[k >> 2] >> (8 * (k & 3u)));
+        }
+    }
+}
+
 // ======================================================= String-dictionary
 // Group-Parallel (Sec. 5: each word is a group that expands to its entry's
 // bytes).  One wave takes whole groups of 64 tokens [t.a, t.b): lane i reads

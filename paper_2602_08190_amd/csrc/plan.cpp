@@ -304,13 +304,16 @@ static void flatten(WorkTables &w, std::vector<uint8_t> &host, uint64_t off, uin
         const uint32_t c = w.chunks[t.chunk].codec;
         A.sdict_codecs |= c == C_SDICT_COL || c == C_SDICT_COL_ANS ? 1u : 2u;
     }
-    A.ans_load = 0;
-    if (!w.tiles[K_ANS].empty()) {
+    // (longest first: tile 0 is the largest)
+    auto load = [&](Kind k, uint32_t &most) {
         uint64_t sum = 0;
-        for (const Tile &t : w.tiles[K_ANS]) sum += unit_bytes(w.chunks[t.chunk]);
-        const uint64_t most = std::max<uint64_t>(1, unit_bytes(w.chunks[w.tiles[K_ANS][0].chunk]));
-        A.ans_load = uint32_t(sum / most);
-    }
+        for (const Tile &t : w.tiles[k]) sum += unit_bytes(w.chunks[t.chunk]);
+        most = w.tiles[k].empty() ? 0 : uint32_t(unit_bytes(w.chunks[w.tiles[k][0].chunk]));
+        return uint32_t(sum / std::max(1u, most));
+    };
+    uint32_t most;
+    A.lz_load = load(K_LZ, A.lz_bytes);
+    A.ans_load = load(K_ANS, most);
 }
 
 struct DeviceGuard {
@@ -496,6 +499,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
         A.err = P->d_err;
         A.counter = P->d_err + 64;
         A.fat = P->d_fat;
+        A.lz_whole = !o.tiles[K_LZ].unit && !o.tiles[K_LZ].waves_per_block;
     };
     fill(P->image_args);
     for (uint32_t k = 0; k < P->batches.size(); k++) {

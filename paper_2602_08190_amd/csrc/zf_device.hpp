@@ -99,6 +99,8 @@ struct LaunchArgs {
     uint32_t kind_begin[K_COUNT + 1];
     uint32_t two_stage;           // some units read the scratch area that earlier kinds write
     uint32_t sdict_codecs;        // String-dictionary tiles: bit 0 some over a column dictionary, bit 1 some not
+    uint32_t lz_bytes, lz_load;   // bytes of the largest LZ77 tile; of all / of the largest
+    uint32_t lz_whole;            // may a workgroup decode a whole LZ77 chunk in LDS (no tile shape was asked for)?
     uint32_t ans_load;            // bytes of all ANS tiles / bytes of the largest
 };
 

@@ -7,6 +7,7 @@ import oracle.zfo as zo
 from paper_2602_08190_amd import datagen as g
 from paper_2602_08190_amd import zf
 
+import helpers as H
 from conftest import gpu_available
 from test_gpu_parity import check, decode_image, decode_staged, log, torch
 
@@ -163,3 +164,64 @@ def test_spans_of_the_run_map(dtype, unit):
         col = zf.Column.compress(big, zf.RLE_DELTA_BP, chunk_elems=[len(big)])
         out, = decode_image([col])
         assert np.array_equal(out, big)
+
+
+def lz_containers():
+    """Streams for the workgroup LZ77 kernel: batches of 64 matches of 33 and
+    36 bytes (more pieces than a wave lists), a group of 512 sequences that
+    all take two extension words, literal runs of 1 to 5,000 bytes, matches of
+    every length 4..70, overlapping and long ones, empty sequences, batches
+    that are not flat, chunks of 1..67 bytes and of 64 KiB."""
+    r = g.rng(42)
+    out = []
+
+    def add(seqs, plain):
+        nlit = sum(s[0] for s in seqs)
+        out.append((H.lz_stream(seqs, r.bytes(nlit), plain), plain, zf.LZ77))
+
+    def total(seqs):
+        return sum(a + b for a, b, _ in seqs)
+    for ml in (33, 36):
+        seqs = [(4096, 0, 0)] + [(0, 0, 0)] * 63 + [(0, ml, int(r.integers(ml + 64 * ml, 4000))) for _ in range(640)]
+        add(seqs, total(seqs))
+    seqs = [(900, 0, 0)] + [(0, 0, 0)] * 63 + [(7 + i % 3, 34 + i % 5, 1 + (i * 7) % 6) for i in range(600)]
+    add(seqs, total(seqs))
+    seqs = [(n, 0, 0) for n in (1, 2, 3, 4, 5, 31, 32, 33, 255, 256, 257, 1023, 1025, 5000)]
+    add(seqs, total(seqs))
+    seqs = [(3000, 0, 0)] + [(0, 0, 0)] * 63 + [(i % 4, 4 + i % 67, 2900 - i % 60) for i in range(500)]
+    add(seqs, total(seqs))
+    for n in list(range(1, 68)) + [65535, 65536]:
+        for gen in (H.random_lz, H.flat_lz):
+            seqs, lits = gen(r, n)
+            out.append((H.lz_stream(seqs, lits, n), n, zf.LZ77))
+    seqs, lits = H.flat_lz(r, 40_000, empty_every=3)
+    out.append((H.lz_stream(seqs, lits, 40_000), 40_000, zf.LZ77))
+    return out
+
+
+def test_lz_chunk_kernel_streams():
+    chunks = lz_containers()
+    log("lz chunk kernel,", len(chunks), "streams")
+    blob = H.container(zf.BYTES, chunks)
+    col = zf.Column.from_bytes(blob)
+    check([col], decode_image([col]))
+    check([col], decode_image([col], tiles={"LZ77": dict(unit=4)}))
+
+
+@pytest.mark.parametrize("kind", ["zeros", "random", "dates", "period"])
+@pytest.mark.parametrize("ce", [8192, 16384])
+def test_lz_chunk_kernel_columns(kind, ce):
+    n = 100_003
+    x = {"zeros": np.zeros(n, np.int32), "random": np.frombuffer(g.rng(1).bytes(4 * n), np.int32),
+         "dates": g.sorted_runs_column(n, 8, 3), "period": np.resize(np.arange(25, dtype=np.int32), n)}[kind]
+    col = zf.Column.compress(x, zf.LZ77, chunk_elems=[1, ce] + [ce - 1] * (n // ce - 1) + [n - 1 - ce - (ce - 1) * (n // ce - 1)]
+                             if kind != "zeros" else [ce] * (n // ce) + [n % ce])
+    check([col], decode_image([col]), [x])
+
+
+def test_lz_past_the_chunk_kernels_limit():
+    # more tiny chunks than the workgroup kernel takes: the one-wave kernel
+    n = 5 * 4 * cus() + 7
+    x = g.text_column(20 * n, 9)
+    col = zf.Column.compress(x, zf.LZ77, chunk_elems=[20] * n)
+    check([col], decode_image([col]), [x])
