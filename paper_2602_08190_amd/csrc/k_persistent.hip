@@ -1,6 +1,7 @@
 // The persistent multi-codec kernel, the small helper kernels and the host
 // entry that enqueues a launch's decode.
 #include "kernels.hpp"
+#include "plan.hpp"
 
 namespace zf {
 
@@ -52,7 +53,52 @@ __global__ void k_set_out_tab(uint8_t **tab, OutTable t, uint32_t n) {
     if (i < n) tab[i] = t.p[i];
 }
 
+// A batch's transfer, read from pinned host memory over the link by a few
+// workgroups, a piece each at a time, 16 KiB in flight per workgroup.  Against
+// a copy command per column range, each of which costs the host and the copy
+// engine about 10 us: a staged 16-column table of 500,009 rows in three batches
+// 826 -> 516 us (host 960 -> 130 us), 20,011 rows in one 330 -> 180 us.  16
+// workgroups carry what the link does (1 MiB 21.5 us, a copy command 27; 8 MiB
+// 150 and 156; 256 MiB both 57 GB/s).  Each asks for a compute unit's whole
+// LDS, to share it with no wave that waits for memory in step with others:
+// loads of one compute unit return in order, and those of a decode beside the
+// copy would wait for the link's (the ANS stage 97 us alone, 150 to 207 us
+// beside the copy without this; the table 591 us).
+constexpr uint32_t kCopyBlocks = 16, kCopyLds = 160 * 1024;
+__global__ __launch_bounds__(256) void k_copy(const CopyPiece *tab, uint32_t n) {
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const CopyPiece p = tab[i];
+        const ZF_GLOBAL uint8_t *src = gp(uniform_ptr(p.src));
+        ZF_GLOBAL uint8_t *dst = gp(uniform_ptr(p.dst));
+        uint64_t done = 0;
+        if (((reinterpret_cast<uintptr_t>(p.src) | reinterpret_cast<uintptr_t>(p.dst)) & 15u) == 0) {
+            const ZF_GLOBAL u32x4 *s4 = reinterpret_cast<const ZF_GLOBAL u32x4 *>(src);
+            ZF_GLOBAL u32x4 *d4 = reinterpret_cast<ZF_GLOBAL u32x4 *>(dst);
+            const uint32_t nv = uint32_t(p.len / 16);
+            for (uint32_t k = threadIdx.x; k < nv; k += 4 * 256) {
+                u32x4 v[4];
+#pragma unroll
+                for (uint32_t u = 0; u < 4; u++)
+                    if (k + 256 * u < nv) v[u] = __builtin_nontemporal_load(s4 + k + 256 * u);
+#pragma unroll
+                for (uint32_t u = 0; u < 4; u++)
+                    if (k + 256 * u < nv) d4[k + 256 * u] = v[u];
+            }
+            done = 16ull * nv;
+        }
+        for (uint64_t k = done + threadIdx.x; k < p.len; k += 256) dst[k] = src[k];
+    }
+}
+
 // ============================================================ host side
+hipError_t launch_copy(const CopyPiece *tab, uint32_t n, hipStream_t st) {
+    if (!n) return hipSuccess;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_copy), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              int(kCopyLds));
+    hipLaunchKernelGGL(k_copy, dim3(n < kCopyBlocks ? n : kCopyBlocks), dim3(256), kCopyLds, st, tab, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n, uint8_t *scratch,
                               hipStream_t st) {
     OutTable t{};

@@ -12,6 +12,16 @@ hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const u
                          uint32_t lz_blk, hipStream_t st, KindEvents *ev = nullptr);
 hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n, uint8_t *scratch, hipStream_t st);
 
+// One piece of a batch's transfer as the copy kernel takes it (device view of
+// the pinned host bytes).
+struct CopyPiece {
+    const uint8_t *src;
+    uint8_t *dst;
+    uint64_t len;
+};
+constexpr uint64_t kCopyRange = 32ull << 20;  // mean bytes of a range from which copy commands carry a batch
+hipError_t launch_copy(const CopyPiece *tab, uint32_t n, hipStream_t st);
+
 struct CopyOp {
     const uint8_t *src;  // pinned host bytes of a column
     uint64_t dst_off;    // offset in the staging slot (or dictionary area)
@@ -42,6 +52,7 @@ struct Batch {
     uint32_t index = 0;     // position in column order, before ordering
     LaunchArgs args{};      // comp base = its slot
     int slot = 0;
+    uint32_t piece0 = 0, n_pieces = 0;  // its pieces in the plan's table (none: copy commands)
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
 };
@@ -73,6 +84,7 @@ struct zf_plan {
     uint64_t scratch_bytes = 0;
     uint64_t dict_bytes = 0;
     std::vector<zf::CopyOp> dict_copies;
+    zf::CopyPiece *d_pieces = nullptr;  // the batches' transfers (see CopyPiece)
 
     zf::LaunchArgs image_args{};    // comp/dict bases filled per call
     std::vector<zf::Batch> batches; // in execution order

@@ -35,31 +35,38 @@ void transfer_and_decompress(zf_plan_t *P, void *const *d_out, hipStream_t st, z
     set_outputs(P, d_out, st);
     // copies start after everything already queued on `st` (including the
     // previous call's decodes, which read the same slots)
+    // (events that only measure are left out of a call that asks for no times)
     ZF_HIP(hipEventRecord(P->ev_start, st));
     ZF_HIP(hipStreamWaitEvent(P->copy_stream, P->ev_start, 0));
-    for (auto &cp : P->dict_copies)
-        ZF_HIP(hipMemcpyAsync(P->d_dict + cp.dst_off, cp.src, cp.len, hipMemcpyHostToDevice, P->copy_stream));
-    ZF_HIP(hipEventRecord(P->ev_dict, P->copy_stream));
-    ZF_HIP(hipStreamWaitEvent(st, P->ev_dict, 0));
+    if (P->batches.empty() || !P->batches[0].n_pieces) {  // (else with the first batch)
+        for (auto &cp : P->dict_copies)
+            ZF_HIP(hipMemcpyAsync(P->d_dict + cp.dst_off, cp.src, cp.len, hipMemcpyHostToDevice, P->copy_stream));
+        ZF_HIP(hipEventRecord(P->ev_dict, P->copy_stream));
+        ZF_HIP(hipStreamWaitEvent(st, P->ev_dict, 0));
+    }
     const size_t ns = P->d_slots.size();
     for (size_t k = 0; k < P->batches.size(); k++) {
         Batch &b = P->batches[k];
         const int s = b.slot;
         if (k >= ns) ZF_HIP(hipStreamWaitEvent(P->copy_stream, P->slot_free[s], 0));
-        ZF_HIP(hipEventRecord(P->ev_h2d0[k], P->copy_stream));
-        for (auto &cp : b.copies)
-            ZF_HIP(hipMemcpyAsync(P->d_slots[s] + cp.dst_off, cp.src, cp.len, hipMemcpyHostToDevice,
-                                  P->copy_stream));
-        ZF_HIP(hipEventRecord(P->ev_h2d1[k], P->copy_stream));
+        if (timing) ZF_HIP(hipEventRecord(P->ev_h2d0[k], P->copy_stream));
+        if (b.n_pieces) {
+            ZF_HIP(launch_copy(P->d_pieces + b.piece0, b.n_pieces, P->copy_stream));
+        } else {
+            for (auto &cp : b.copies)
+                ZF_HIP(hipMemcpyAsync(P->d_slots[s] + cp.dst_off, cp.src, cp.len, hipMemcpyHostToDevice,
+                                      P->copy_stream));
+        }
+        if (timing) ZF_HIP(hipEventRecord(P->ev_h2d1[k], P->copy_stream));
         ZF_HIP(hipEventRecord(P->slot_full[s], P->copy_stream));
         ZF_HIP(hipStreamWaitEvent(st, P->slot_full[s], 0));
-        ZF_HIP(hipEventRecord(P->ev_dec0[k], st));
+        if (timing) ZF_HIP(hipEventRecord(P->ev_dec0[k], st));
         if (b.exec) ZF_HIP(hipGraphLaunch(b.exec, st));
         else ZF_HIP(launch_decode(b.args, P->persistent_waves, b.w.wpb, P->lz_blk, st));
-        ZF_HIP(hipEventRecord(P->ev_dec1[k], st));
-        ZF_HIP(hipEventRecord(P->slot_free[s], st));
+        if (timing) ZF_HIP(hipEventRecord(P->ev_dec1[k], st));
+        if (k + ns < P->batches.size()) ZF_HIP(hipEventRecord(P->slot_free[s], st));
     }
-    ZF_HIP(hipEventRecord(P->ev_end, st));
+    if (timing) ZF_HIP(hipEventRecord(P->ev_end, st));
     P->pending_timing = timing;
     P->timing_valid = true;
 }

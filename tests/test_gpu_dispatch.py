@@ -225,3 +225,44 @@ def test_lz_past_the_chunk_kernels_limit():
     x = g.text_column(20 * n, 9)
     col = zf.Column.compress(x, zf.LZ77, chunk_elems=[20] * n)
     check([col], decode_image([col]), [x])
+
+
+@pytest.mark.parametrize("pinned", [True, False, None])
+@pytest.mark.parametrize("slot", [1 << 12, 100_001, 1 << 22])
+def test_staged_copies(pinned, slot):
+    # transfers by the copy kernel (every column pinned), by copy commands
+    # (none pinned, or one that is not), over one to many batches, three calls
+    # in a row into other outputs
+    xs = [g.uniform_i32(20_000, 5, 1 << 14, 1), g.fixed16_column(7_003, 300, 2), g.text_column(60_001, 3),
+          g.text_column(44_444, 4), g.sorted_runs_column(30_011, 8, 5), np.zeros(0, np.int32)]
+    codecs = [zf.FOR_BP, zf.DICT_BP, zf.SDICT_COL_ANS, zf.LZ77, zf.RLE_DELTA_BP, zf.FOR_BP]
+    cols = [zf.Column.compress(x, c, chunk_bytes=(1 << 12, 1 << 14), seed=i,
+                               pinned=(i != 2 if pinned is None else pinned))
+            for i, (x, c) in enumerate(zip(xs, codecs))]
+    plan = zf.Plan(cols, slot_bytes=slot)
+    for timing in (False, True, False):
+        outs = zf.empty_outputs(cols)
+        plan.transfer_and_decompress(outs, timing=timing)
+        t = plan.sync()
+        if timing:
+            assert t["wall_ms"] > 0 and t["h2d_ms"] > 0 and t["plain_bytes"] == sum(x.nbytes for x in xs)
+        check(cols, [o.cpu().numpy() for o in outs], xs)
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_staged_copies_of_long_ranges(first):
+    # a batch of one long range goes by a copy command, the others by the
+    # copy kernel, the dictionary with the first batch whichever that is
+    xs = [np.frombuffer(g.rng(7).bytes(33 << 20), np.uint8), g.fixed16_column(70_003, 300, 2),
+          g.text_column(300_001, 3)]
+    codecs = [zf.PLAIN, zf.DICT_BP, zf.SDICT_COL]
+    if first:
+        xs, codecs = xs[::-1], codecs[::-1]
+    cols = [zf.Column.compress(x, c, seed=i, pinned=True) for i, (x, c) in enumerate(zip(xs, codecs))]
+    plan = zf.Plan(cols, slot_bytes=34 << 20, order=1)
+    for _ in range(2):
+        outs = zf.empty_outputs(cols)
+        plan.transfer_and_decompress(outs)
+        plan.sync()
+        for o, x in zip(outs, xs):
+            assert np.array_equal(o.cpu().numpy().reshape(-1).view(np.uint8), x.reshape(-1).view(np.uint8))
