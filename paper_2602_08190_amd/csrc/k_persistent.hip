@@ -99,11 +99,9 @@ hipError_t launch_copy(const CopyPiece *tab, uint32_t n, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n, uint8_t *scratch,
-                              hipStream_t st) {
+hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n, hipStream_t st) {
     OutTable t{};
     for (uint32_t i = 0; i < n && i < kScratchCol; i++) t.p[i] = ptrs[i];
-    t.p[kScratchCol] = scratch;
     hipLaunchKernelGGL(k_set_out_tab, dim3(1), dim3(kMaxCols), 0, st, d_tab, t, kMaxCols);
     return hipGetLastError();
 }
@@ -111,9 +109,14 @@ hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n,
 // Enqueue the decode of one launch's units.  persistent_waves > 0 selects
 // the persistent kernel with that many waves in flight.  With `ev`, an event
 // is recorded on `st` before and after each kind's launch (slot K_COUNT: the
-// persistent kernel), and ev->used says which were recorded.
+// persistent kernel), and ev->used says which were recorded.  With `side`, the
+// kinds that depend on none of LZ77, ANS and String-dictionary may be launched
+// on its stream beside those: a chain of whole-chunk units that leaves most of
+// the GPU idle takes about 100 us whatever else there is.  (With more such
+// units the kinds compete instead.)  16 columns, one of them text, 1,500,007
+// rows: 226 us one after the other, 202 us beside; 20,011 rows: 123 and 118 us.
 hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const uint32_t *wpb,
-                         uint32_t lz_blk, hipStream_t st, KindEvents *ev) {
+                         uint32_t lz_blk, hipStream_t st, KindEvents *ev, const SideStream *side) {
     if (ev)
         for (uint32_t k = 0; k <= K_COUNT; k++) ev->used[k] = false;
     if (A.kind_begin[K_COUNT] == 0) return hipSuccess;
@@ -142,11 +145,20 @@ hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const u
     // launch order: the slow serial kinds first
     // (TREE after the RLE kinds, which write its chunks' run starts; SDICT
     // after ANS, which writes its chunks' entry indices)
-    static const uint32_t order[K_COUNT] = {K_LZ,     K_ANS,    K_RLE32, K_RLE64, K_TREE, K_SDICT, K_DICT128,
-                                            K_DICT64, K_DICT32, K_FOR64, K_FOR32, K_F2I,  K_PLAIN};
+    static const uint32_t order[K_COUNT] = {K_LZ,     K_ANS,    K_SDICT,  K_RLE32,  K_RLE64, K_TREE, K_DICT128,
+                                            K_DICT64, K_DICT32, K_FOR64, K_FOR32, K_F2I,   K_PLAIN};
+    auto count = [&](uint32_t k) { return A.kind_begin[k + 1] - A.kind_begin[k]; };
+    const uint32_t chain = count(K_LZ) + count(K_ANS), rest = A.kind_begin[K_COUNT] - chain - count(K_SDICT);
+    const hipStream_t main = st;
+    const bool fork = side && !ev && chain && rest && A.ans_load <= 8 * cu_count() && A.lz_load <= 2 * cu_count();
+    if (fork) {
+        if ((e = hipEventRecord(side->fork, main)) != hipSuccess) return e;
+        if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return e;
+    }
     for (uint32_t i = 0; i < K_COUNT; i++) {
         const uint32_t k = order[i];
         if (A.kind_begin[k + 1] == A.kind_begin[k]) continue;
+        st = fork && k != K_LZ && k != K_ANS && k != K_SDICT ? side->stream : main;
         if ((e = mark(k, false)) != hipSuccess) return e;
         switch (k) {
         case K_LZ: launch_lz(A, wpb[K_LZ], lz_blk, st); break;
@@ -165,6 +177,10 @@ hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const u
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = mark(k, true)) != hipSuccess) return e;
+    }
+    if (fork) {
+        if ((e = hipEventRecord(side->join, side->stream)) != hipSuccess) return e;
+        if ((e = hipStreamWaitEvent(main, side->join, 0)) != hipSuccess) return e;
     }
     return hipSuccess;
 }

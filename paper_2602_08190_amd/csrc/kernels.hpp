@@ -137,6 +137,13 @@ ZF_DEV void flag(uint32_t *err, uint32_t bits) {
     if (lane_id() == 0) atomicOr(err, bits);
 }
 
+// Output base of a chunk's column (or the scratch area).
+ZF_DEV uint8_t *out_of(const LaunchArgs &A, const ChunkDesc &ck) {
+    const uint32_t col = first32(ck.col);
+    if (col == kScratchCol) return A.scratch;
+    return A.inline_outs ? A.outs[col] : A.out_tab[col];
+}
+
 ZF_DEV uint32_t ld32u(const uint8_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
 ZF_DEV uint64_t ld64u(const uint8_t *p) {
     return uint64_t(ld32u(p)) | (uint64_t(ld32u(p + 4)) << 32);
@@ -587,7 +594,7 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len;
     const uint32_t nb = (n + kForBlock - 1) / kForBlock;
-    uint8_t *out = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *out = out_of(A, ck) + ck.out_off;
     const uint8_t *dict = A.dict + ck.dict_off;
     if (16ull * nb > clen || t.a + t.b > nb) {
         flag(A.err, ERR_CORRUPT);
@@ -651,7 +658,7 @@ ZF_DEV void unit_f2i(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
     const uint32_t nb = (n + kForBlock - 1) / kForBlock;
-    uint8_t *out = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *out = out_of(A, ck) + ck.out_off;
     if (32ull * nb > clen || t.a + t.b > nb) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -873,7 +880,7 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
     const bool unit_runs = ck.codec == C_DELTA_BP;
-    U *out = reinterpret_cast<U *>(A.out_tab[ck.col] + ck.out_off);
+    U *out = reinterpret_cast<U *>(out_of(A, ck) + ck.out_off);
     if (clen < 16) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -1031,7 +1038,7 @@ ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc
     constexpr uint32_t BITS = sizeof(U) * 8;
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t R = ck.n_elems, clen = ck.comp_len, lane = lane_id();
-    U *out = reinterpret_cast<U *>(A.out_tab[kScratchCol] + ck.out_off);
+    U *out = reinterpret_cast<U *>(A.scratch + ck.out_off);
     if (clen < 32) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -1114,8 +1121,8 @@ template <class U>
 ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *map) {
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
-    U *out = reinterpret_cast<U *>(A.out_tab[ck.col] + ck.out_off);
-    const U *S = reinterpret_cast<const U *>(A.out_tab[kScratchCol] + ck.aux_off);
+    U *out = reinterpret_cast<U *>(out_of(A, ck) + ck.out_off);
+    const U *S = reinterpret_cast<const U *>(A.scratch + ck.aux_off);
     if (clen < 32) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -1358,7 +1365,7 @@ ZF_DEV void unit_lz(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *row) {
     const uint32_t clen = ck.comp_len, lane = lane_id();
     const uint32_t es = ck.dtype == D_I32 ? 4 : ck.dtype == D_I64 ? 8 : ck.dtype == D_FIXED16 ? 16 : 1;
     const uint32_t plain = ck.n_elems * es;
-    uint8_t *out = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *out = out_of(A, ck) + ck.out_off;
     if (clen < 16) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -1497,7 +1504,7 @@ ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
     const uint32_t clen = ck.comp_len, lane = lane_id(), w = first32(threadIdx.x / 64);
     const uint32_t es = ck.dtype == D_I32 ? 4 : ck.dtype == D_I64 ? 8 : ck.dtype == D_FIXED16 ? 16 : 1;
     const uint32_t plain = ck.n_elems * es;
-    uint8_t *out = uniform_ptr(A.out_tab[ck.col] + ck.out_off);
+    uint8_t *out = uniform_ptr(out_of(A, ck) + ck.out_off);
     if (clen < 16) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -1773,7 +1780,7 @@ ZF_DEV void unit_sdict_t(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck
     constexpr bool kSmall = kSdHold + 64 * kSdMaxToken > 4 * kWords;
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t lane = lane_id(), plain = ck.n_elems, clen = ck.comp_len;
-    uint8_t *out = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *out = out_of(A, ck) + ck.out_off;
     constexpr bool coldict = COL;
     const bool staged = ck.codec == C_SDICT_ANS || ck.codec == C_SDICT_COL_ANS;
     uint32_t nt = 0, ne = 0, w = 0, ng = 0, co = 0, nb = 0, go = 0;
@@ -1827,7 +1834,7 @@ ZF_DEV void unit_sdict_t(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck
     // Index words, entries and group offsets are read through bounds-checked
     // views (a read past a view returns 0), so no load sits behind a branch
     // and loads stay in flight until their values are used.
-    const uint8_t *codes = uniform_ptr(staged ? A.out_tab[kScratchCol] + ck.aux_off : s + co);
+    const uint8_t *codes = uniform_ptr(staged ? A.scratch + ck.aux_off : s + co);
     const __amdgpu_buffer_rsrc_t rs_codes =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(codes), 0, int(4 * ncw), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_ents =
@@ -2303,7 +2310,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     const uint32_t es = ck.dtype == D_I32 ? 4 : (ck.dtype == D_I64 || ck.dtype == D_F64) ? 8
                         : ck.dtype == D_FIXED16 ? 16 : 1;
     const uint32_t n = ck.n_elems * es;
-    uint8_t *out = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *out = out_of(A, ck) + ck.out_off;
     // sizes, the frequency total and every coder's word range are checked
     // here before any of them is used (the host checked them too)
     if (ck.comp_len < kAnsHdr) {
@@ -2481,7 +2488,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
 // ================================================================ PLAIN
 ZF_DEV void unit_plain(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) {
     const uint8_t *src = A.comp + ck.comp_off;
-    uint8_t *dst = A.out_tab[ck.col] + ck.out_off;
+    uint8_t *dst = out_of(A, ck) + ck.out_off;
     const uint32_t a = t.a, b = min(t.b, ck.comp_len), lane = lane_id();
     if (((reinterpret_cast<uintptr_t>(src + a) | reinterpret_cast<uintptr_t>(dst + a)) & 15u) == 0) {
         const uint32_t nvec = (b - a) / 16;
@@ -2612,7 +2619,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 }
 void launch_lz(const LaunchArgs &A, uint32_t waves, uint32_t blk, hipStream_t st);
 hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const uint32_t *wpb,
-                         uint32_t lz_blk, hipStream_t st, KindEvents *ev);
+                         uint32_t lz_blk, hipStream_t st, KindEvents *ev, const SideStream *side);
 
 void launch_ans(const LaunchArgs &A, uint32_t waves, hipStream_t st);
 

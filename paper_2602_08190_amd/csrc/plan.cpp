@@ -496,6 +496,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
 
     auto fill = [&](LaunchArgs &A) {
         A.out_tab = P->d_out_tab;
+        A.scratch = P->d_scratch;
         A.err = P->d_err;
         A.counter = P->d_err + 64;
         A.fat = P->d_fat;
@@ -579,6 +580,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     ZF_HIP(hipEventCreate(&P->ev_start));
     ZF_HIP(hipEventCreate(&P->ev_end));
     ZF_HIP(hipEventCreateWithFlags(&P->ev_dict, hipEventDisableTiming));
+    ZF_HIP(hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming));
 
     if (o.use_graphs && !P->batches.empty()) {
         hipStream_t cap;
@@ -621,7 +623,7 @@ void release_plan(zf_plan_t *P) {
     kill(p.ev_h2d1);
     kill(p.ev_dec0);
     kill(p.ev_dec1);
-    for (auto e : {p.ev_start, p.ev_end, p.ev_dict})
+    for (auto e : {p.ev_start, p.ev_end, p.ev_dict, p.ev_join})
         if (e) (void)hipEventDestroy(e);
     for (uint32_t k = 0; k <= K_COUNT; k++)
         for (auto e : {p.kind_ev.e0[k], p.kind_ev.e1[k]})

@@ -4,7 +4,7 @@
 
 namespace zf {
 
-static void set_outputs(zf_plan_t *P, void *const *d_out, hipStream_t st) {
+static void check_outputs(zf_plan_t *P, void *const *d_out) {
     const uint32_t n = uint32_t(P->cols.size());
     ZF_REQUIRE(d_out, ZF_E_INVALID, "null output table");
     for (uint32_t c = 0; c < n; c++) {
@@ -13,7 +13,10 @@ static void set_outputs(zf_plan_t *P, void *const *d_out, hipStream_t st) {
         ZF_REQUIRE((reinterpret_cast<uintptr_t>(d_out[c]) & 15u) == 0, ZF_E_INVALID,
                    "output %u is not 16-byte aligned", c);
     }
-    ZF_HIP(launch_set_out_tab(P->d_out_tab, reinterpret_cast<uint8_t *const *>(d_out), n, P->d_scratch, st));
+}
+
+static void set_out_tab(zf_plan_t *P, void *const *d_out, hipStream_t st) {
+    ZF_HIP(launch_set_out_tab(P->d_out_tab, reinterpret_cast<uint8_t *const *>(d_out), uint32_t(P->cols.size()), st));
 }
 
 void decompress_async(zf_plan_t *P, const void *d_comp, uint64_t comp_bytes, void *const *d_out,
@@ -21,18 +24,28 @@ void decompress_async(zf_plan_t *P, const void *d_comp, uint64_t comp_bytes, voi
     ZF_REQUIRE(d_comp || P->image_bytes == 0, ZF_E_INVALID, "null device image");
     ZF_REQUIRE(comp_bytes >= P->image_bytes, ZF_E_TOO_SMALL, "device image holds %llu bytes, plan needs %llu",
                (unsigned long long)comp_bytes, (unsigned long long)P->image_bytes);
-    set_outputs(P, d_out, st);
+    check_outputs(P, d_out);
     LaunchArgs A = P->image_args;
     A.comp = static_cast<const uint8_t *>(d_comp);
     A.dict = static_cast<const uint8_t *>(d_comp);
-    ZF_HIP(launch_decode(A, P->persistent_waves, P->image_wpb, P->lz_blk, st,
-                         P->profile ? &P->kind_ev : nullptr));
+    // the output pointers travel with the launches; more columns than fit go
+    // through the device table, a launch of its own in every call (10,007
+    // values in one column: 10.5 us with it, 7 us without)
+    A.inline_outs = P->cols.size() <= kInlineOuts;
+    if (A.inline_outs)
+        for (size_t c = 0; c < P->cols.size(); c++) A.outs[c] = static_cast<uint8_t *>(d_out[c]);
+    else
+        set_out_tab(P, d_out, st);
+    const SideStream side{P->copy_stream, P->ev_dict, P->ev_join};
+    ZF_HIP(launch_decode(A, P->persistent_waves, P->image_wpb, P->lz_blk, st, P->profile ? &P->kind_ev : nullptr,
+                         &side));
     if (P->profile) P->kinds_recorded = true;
     P->timing_valid = false;
 }
 
 void transfer_and_decompress(zf_plan_t *P, void *const *d_out, hipStream_t st, zf_timing *timing) {
-    set_outputs(P, d_out, st);
+    check_outputs(P, d_out);
+    set_out_tab(P, d_out, st);
     // copies start after everything already queued on `st` (including the
     // previous call's decodes, which read the same slots)
     // (events that only measure are left out of a call that asks for no times)

@@ -13,6 +13,8 @@ constexpr uint32_t kMaxCols = 256;     // output table size: columns per plan + 
 // Output-table slot of the plan's scratch area (the decoded entry indices of
 // String-dictionary | BP | ANS chunks, the first of their two decode stages)
 constexpr uint32_t kScratchCol = kMaxCols - 1;
+// Output pointers a launch's arguments hold (more columns: the table)
+constexpr uint32_t kInlineOuts = 32;
 // ANS: M = 2^12 model, state in [2^16, 2^32), 64 interleaved coders, stream
 // header of 16 + 512 (frequencies) + 256 (states) + 256 (word offsets) bytes.
 constexpr uint32_t kAnsM = 4096, kAnsL = 65536, kAnsLanes = 64, kAnsHdr = 784;
@@ -90,7 +92,8 @@ enum : uint32_t { ERR_CORRUPT = 1u, ERR_BOUNDS = 2u };
 struct LaunchArgs {
     const uint8_t *comp;          // base of the compressed streams
     const uint8_t *dict;          // base of the dictionaries
-    uint8_t *const *out_tab;      // device table: column -> output pointer
+    uint8_t *const *out_tab;      // device table: column -> output pointer (used where inline_outs is 0)
+    uint8_t *scratch;             // the plan's scratch area
     const ChunkDesc *chunks;
     const Tile *tiles;            // tiles grouped by kind
     uint32_t *err;                // device error word
@@ -99,9 +102,18 @@ struct LaunchArgs {
     uint32_t kind_begin[K_COUNT + 1];
     uint32_t two_stage;           // some units read the scratch area that earlier kinds write
     uint32_t sdict_codecs;        // String-dictionary tiles: bit 0 some over a column dictionary, bit 1 some not
+    uint32_t inline_outs;         // the output pointers are here (a call's own arguments need no table)
+    uint8_t *outs[kInlineOuts];
     uint32_t lz_bytes, lz_load;   // bytes of the largest LZ77 tile; of all / of the largest
     uint32_t lz_whole;            // may a workgroup decode a whole LZ77 chunk in LDS (no tile shape was asked for)?
     uint32_t ans_load;            // bytes of all ANS tiles / bytes of the largest
+};
+
+// Host side: a second stream, and the events that order work on it after the
+// caller's stream and the caller's stream after it.
+struct SideStream {
+    hipStream_t stream;
+    hipEvent_t fork, join;
 };
 
 // Host side: events recorded around each kind's launch of a profiled decode

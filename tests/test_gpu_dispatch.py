@@ -266,3 +266,43 @@ def test_staged_copies_of_long_ranges(first):
         plan.sync()
         for o, x in zip(outs, xs):
             assert np.array_equal(o.cpu().numpy().reshape(-1).view(np.uint8), x.reshape(-1).view(np.uint8))
+
+
+@pytest.mark.parametrize("n_cols", [1, 32, 33, 70])
+@pytest.mark.parametrize("chain", [zf.LZ77, zf.ANS, zf.SDICT_COL_ANS, None])
+def test_forked_launches_and_output_pointers(n_cols, chain):
+    # output pointers with the launch (up to 32 columns) or in the table, and
+    # kinds beside a chain of whole-chunk units on a second stream: two sets of
+    # outputs in turn without a wait between, then a captured decode replayed
+    T = torch()
+    kinds = [(zf.FOR_BP, lambda i: g.uniform_i32(3_001 + i, 5, 1 << 14, i)),
+             (zf.RLE_DELTA_BP, lambda i: g.sorted_runs_column(2_011 + i, 8, i)),
+             (zf.DICT_BP, lambda i: g.fixed16_column(1_003 + i, 30, i))]
+    xs, cols = [], []
+    for i in range(n_cols):
+        if chain is not None and i % 4 == 0:
+            x, c = g.text_column(5_003 + i, i), chain
+        else:
+            c, make = kinds[i % 3]
+            x = make(i)
+        xs.append(x)
+        cols.append(zf.Column.compress(x, c, chunk_bytes=(1 << 10, 1 << 12), seed=i))
+    plan = zf.Plan(cols, device=0)
+    img = zf.upload_image(plan, cols)
+    a, b = zf.empty_outputs(cols), zf.empty_outputs(cols)
+    for outs in (a, b, a):
+        plan.decompress_async(img, img.numel(), outs)
+    plan.sync()
+    check(cols, [o.cpu().numpy() for o in a], xs)
+    check(cols, [o.cpu().numpy() for o in b], xs)
+    graph = T.cuda.CUDAGraph()
+    s = T.cuda.Stream()
+    s.wait_stream(T.cuda.current_stream())
+    with T.cuda.graph(graph, stream=s):
+        plan.decompress_async(img, img.numel(), b, stream=s)
+    for k in range(3):
+        for o in b:
+            o.zero_()
+        graph.replay()
+        T.cuda.synchronize()
+        check(cols, [o.cpu().numpy() for o in b], xs)
