@@ -2287,18 +2287,22 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 //
 // A step is a chain: state -> slot -> model -> state -> who needs a word ->
 // word -> state.  What a chunk costs is that chain's latency while few waves
-// share a SIMD, and the instructions issued per step when many do, so there
-// are two models:
-//   FUSED: one dword per slot {byte, slot - cum, f - 1}, 16 KiB: one LDS
-//     read between the slot and the next state, and the ring holds each word
-//     with the table address it leads to beside it, so that the address is
-//     known two instructions after the word.  Eight waves fit a CU's LDS.
+// share a SIMD (an LDS read is 52 cycles, a vector instruction that uses the
+// one before it 8, any other 4), and the LDS reads per step when many do, so
+// there are two models:
+//   FUSED: one dword per slot {byte, slot - cum, f}, 16 KiB, and the ring holds
+//     each word's entry with its top four bits beside it, looked up when the
+//     word came in.  A step then reads the entry of its new state and the entry
+//     of the next word side by side and takes one of them: one trip to the LDS.
+//     What is carried is the entry and the state's bits above the slot; the
+//     instructions stand in the order of the longest chain, the others in its
+//     gaps.  f = 4096 has no room: a chunk of one byte is filled without a
+//     table.  Eight waves fit a CU's LDS.
 //   else: slot -> byte (4 KiB) and byte -> {f, -cum} (2 KiB): two reads, but
 //     19 waves a CU.
-// 64 KiB chunks of flags, one wave a CU: 150 us with two reads, a ring in
-// registers read by cross-lane permutes and 1.4 times the instructions, 129 us
-// with two reads and this ring, 97 us fused.  4,096 chunks (16 waves a CU, the
-// LDS about 26 cycles a step and wave): 199 -> 179 us.
+// 64 KiB chunks of flags, 64 chunks: 129 us with the second, 97 us with a fused
+// model read after the word, 72 us as it is (62 ns a step); 2,048 chunks (eight
+// a CU, the LDS's reads) 148, 117 and 98 us; 4,096 chunks with the second 179.
 constexpr uint32_t kAnsRing = 512;        // words; a refill brings half of them
 constexpr uint32_t kAnsSteps = 4;         // steps between two looks at the ring (at most 64 words each)
 static_assert(kAnsSteps * kAnsLanes <= kAnsRing / 2, "ANS ring");
@@ -2343,11 +2347,24 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         flag(A.err, ERR_CORRUPT);
         return;
     }
+    // a chunk of one byte, as an encoder writes it (otherwise its states, which
+    // stand still, are followed step by step)
+    const uint64_t single =
+        FUSED ? __ballot(f[0] == kAnsM || f[1] == kAnsM || f[2] == kAnsM || f[3] == kAnsM) : 0ull;
+    if (single && nw == 0 && !any(x != kAnsL)) {
+        const uint32_t b = rl32(4 * lane + (f[1] ? 1 : 0) + (f[2] ? 2 : 0) + (f[3] ? 3 : 0),
+                                uint32_t(__builtin_ctzll(single)));
+        const uint32_t v = b * 0x01010101u, m = (reinterpret_cast<uintptr_t>(out) & 15u) == 0 ? n & ~15u : 0u;
+        for (uint32_t i = 16 * lane; i < m; i += 16 * 64) st16_nt(out + i, v, v, v, v);
+        for (uint32_t i = m + lane; i < n; i += 64) gp(out)[i] = uint8_t(b);
+        return;
+    }
     uint32_t *tab = lds;                                                  // FUSED: slot -> entry
     uint8_t *sym = reinterpret_cast<uint8_t *>(lds);                      // else: slot -> byte
     u32x2 *fc = reinterpret_cast<u32x2 *>(lds + kAnsM / 4);               // and byte -> {f, -cum}
     uint32_t *ring = lds + (FUSED ? kAnsM : kAnsM / 4 + 512);
-    constexpr uint32_t kWordBytes = FUSED ? 4 : 2;                        // of a ring entry
+    constexpr uint32_t kWordBytes = FUSED ? 5 : 2;                        // of a ring entry
+    uint8_t *top = reinterpret_cast<uint8_t *>(ring + kAnsRing + 64);     // FUSED: each word's top four bits
     uint8_t *stg = reinterpret_cast<uint8_t *>(ring) + (kAnsRing + 64) * kWordBytes;  // 1 KiB of output
     {
         // Slot -> byte: bit c - 1 of a 4096-bit map is set for every present
@@ -2365,7 +2382,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         for (uint32_t k = 0; k < 4; k++) {
             const uint32_t b = 4 * lane + k;
             if (f[k]) {
-                list[rank] = FUSED ? b + ((f[k] - 1) << 20) - (c << 8) : b;
+                list[rank] = FUSED ? b + (f[k] << 20) - (c << 8) : b;
                 if (c)
                     __hip_atomic_fetch_or(map + ((c - 1) >> 5), 1u << ((c - 1) & 31u), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2388,15 +2405,23 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     }
     wave_fence();
     uint32_t pos = 0, filled = 0;  // words taken; words brought into the ring
+    // FUSED: the model's entry of x's slot
+    auto entry = [&](uint32_t v) {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(tab) + ((v << 2) & 0x3FFCu));
+    };
     auto refill = [&]() {
         // words [filled, filled + 256) into their half of the ring
         const uint32_t at = (filled & (kAnsRing - 1)) + 4 * lane;
         if constexpr (FUSED) {
-            // the word above the table address of the slot it ends in
-            const u32x4 v = {(pre0 << 16) | ((pre0 << 2) & 0x3FFCu), (pre0 & 0xFFFF0000u) | ((pre0 >> 14) & 0x3FFCu),
-                             (pre1 << 16) | ((pre1 << 2) & 0x3FFCu), (pre1 & 0xFFFF0000u) | ((pre1 >> 14) & 0x3FFCu)};
+            const u32x4 v = {entry(pre0), entry(pre0 >> 16), entry(pre1), entry(pre1 >> 16)};
+            const uint32_t t = ((pre0 >> 12) & 0xFu) | ((pre0 >> 20) & 0xF00u) | ((pre1 << 4) & 0xF0000u) |
+                               ((pre1 >> 4) & 0xF000000u);
             *reinterpret_cast<u32x4 *>(ring + at) = v;
-            if (at < 64) *reinterpret_cast<u32x4 *>(ring + kAnsRing + at) = v;
+            *reinterpret_cast<uint32_t *>(top + at) = t;
+            if (at < 64) {
+                *reinterpret_cast<u32x4 *>(ring + kAnsRing + at) = v;
+                *reinterpret_cast<uint32_t *>(top + kAnsRing + at) = t;
+            }
         } else {
             const u32x2 v = {pre0, pre1};
             *reinterpret_cast<u32x2 *>(ring + at / 2) = v;
@@ -2408,46 +2433,61 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     };
     refill();
     refill();
-    // FUSED: the model's entry of x's slot, read as soon as its address is
-    // known (at the end of the step before)
-    auto entry = [&](uint32_t a) {
-        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(tab) + (a & 0x3FFCu));
+    uint32_t e0 = FUSED ? entry(x) : 0u, xs = x >> 12;  // FUSED: what is carried of x
+    auto look = [&]() {
+        if (pos + kAnsRing / 2 > filled) refill();
     };
-    uint32_t e0 = FUSED ? entry(x << 2) : 0u;
-    // one byte per coder: b's low byte
-    auto step = [&](uint32_t &b, bool act) {
-        uint32_t xn;
+    // One byte per coder, b's low byte; then() while the reads are on their way.
+    // (keep: f = 4096)
+    auto step = [&](uint32_t &b, bool act, bool keep, auto &&then) {
         if constexpr (FUSED) {
             b = e0;
-            const uint32_t xs = x >> 12;
-            uint32_t off = xs + ((b >> 8) & 0xFFFu);
-            asm volatile("" : "+v"(off));  // (one multiply-add after the frequency)
-            xn = (b >> 20) * xs + off;
+            uint32_t p0 = pos & (kAnsRing - 1);
+            asm volatile("" : "+v"(p0));  // (the count starts from it)
+            const uint32_t fx = keep ? kAnsM : b >> 20;
+            const uint32_t xn = fx * (xs & 0xFFFFFFu) + ((b >> 8) & 0xFFFu);
+            __builtin_amdgcn_sched_barrier(0);
+            const bool need = act && xn < kAnsL;  // one word at most: x >= 1 * 2^4 before the shift
+            const uint64_t m = __ballot(need);
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t a = (xn << 2) & 0x3FFCu;
+            asm volatile("" : "+v"(a));
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t lo = __builtin_amdgcn_mbcnt_lo(uint32_t(m), p0);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t en = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(tab) + a);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), lo);
+            // (read by every lane and selected: a branch around it costs more)
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t r = ring[at];
+            const uint32_t w = top[at];
+            __builtin_amdgcn_sched_barrier(0);
+            pos += uint32_t(__popcll(m));
+            then();
+            uint32_t xl = xn << 4, xh = xn >> 12;
+            asm volatile("" : "+v"(xl), "+v"(xh));
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t e1 = need ? r : en, xs1 = need ? xl | w : xh;
+            e0 = act ? e1 : e0;
+            xs = act ? xs1 : xs;
         } else {
             const uint32_t slot = x & (kAnsM - 1);
             b = sym[slot];
             const u32x2 e = fc[b];
-            xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
-        }
-        x = act ? xn : x;
-        const bool need = act && x < kAnsL;  // one word at most: x >= 1 * 2^4 before the shift
-        const uint64_t m = __ballot(need);
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-        const uint32_t p0 = pos & (kAnsRing - 1);
-        // (read by every lane and selected: a branch around it costs more)
-        if constexpr (FUSED) {
-            const uint32_t e = ring[p0 + rank];
-            e0 = entry(need ? e : x << 2);
-            __builtin_amdgcn_sched_barrier(0);  // the next step's read before this state's last words
-            const uint32_t xp = alignbit(x, e, 16);
-            x = need ? xp : x;
-        } else {
+            const uint32_t xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
+            x = act ? xn : x;
+            const bool need = act && x < kAnsL;
+            const uint64_t m = __ballot(need);
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+            const uint32_t p0 = pos & (kAnsRing - 1);
             const uint32_t w = reinterpret_cast<const uint16_t *>(ring)[p0 + rank];
             uint32_t xp = (x << 16) | w;
             asm volatile("" : "+v"(xp));
             x = need ? xp : x;
+            pos += uint32_t(__popcll(m));
+            then();
         }
-        pos += uint32_t(__popcll(m));
     };
     bool bad = false;
     const uint32_t steps = (n + kAnsLanes - 1) / kAnsLanes;
@@ -2455,16 +2495,17 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     // caches (512 MiB of text: that launch 338 -> 264 us)
     const bool again = ck.col == kScratchCol;
     uint32_t t = 0;
-    if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
+    if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0 && !single) {
         // 16 steps at a time: each lane's 16 bytes (one per step, 64 apart)
         // gathered in LDS, then written back as 16 contiguous bytes per lane
         for (; t + 16 <= n / kAnsLanes; t += 16) {
 #pragma unroll
             for (uint32_t jj = 0; jj < 16; jj++) {
-                if (jj % kAnsSteps == 0 && pos + kAnsRing / 2 > filled) refill();
                 uint32_t b;
-                step(b, true);
-                stg[64 * jj + lane] = uint8_t(b);
+                step(b, true, false, [&] {
+                    stg[64 * jj + lane] = uint8_t(b);
+                    if (jj % kAnsSteps == kAnsSteps - 1) look();
+                });
             }
             wave_fence();
             const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + 16 * lane);
@@ -2475,13 +2516,13 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         }
     }
     for (; t < steps; t++) {
-        if (pos + kAnsRing / 2 > filled) refill();
         const uint32_t i = t * kAnsLanes + lane;
         uint32_t b;
-        step(b, i < n);
+        step(b, i < n, single != 0, [] {});
+        look();
         if (i < n) __builtin_nontemporal_store(uint8_t(b), gp(out) + i);  // never read back here
     }
-    bad = x != kAnsL || pos != nw;
+    bad = (FUSED ? xs != kAnsL >> 12 || e0 != tab[0] : x != kAnsL) || pos != nw;
     if (any(bad)) flag(A.err, ERR_CORRUPT);
 }
 

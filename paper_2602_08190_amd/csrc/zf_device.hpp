@@ -20,7 +20,7 @@ constexpr uint32_t kInlineOuts = 32;
 constexpr uint32_t kAnsM = 4096, kAnsL = 65536, kAnsLanes = 64, kAnsHdr = 784;
 // ANS: LDS dwords per wave: the model (4 KiB and 2 KiB, or 16 KiB fused), the
 // word ring (576 entries of 2 or 4 bytes) and 1 KiB of output staging
-constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 4096 + 576 + 256;
+constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 4096 + 576 + 144 + 256;
 // String-dictionary: longest token
 constexpr uint32_t kSdMaxToken = 64;
 

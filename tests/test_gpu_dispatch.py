@@ -306,3 +306,39 @@ def test_forked_launches_and_output_pointers(n_cols, chain):
         graph.replay()
         T.cuda.synchronize()
         check(cols, [o.cpu().numpy() for o in b], xs)
+
+
+def test_ans_chunks_of_one_byte():
+    # a byte that holds the whole model, first, last and between, at lengths
+    # around the lanes and steps and off the 16-byte grid; then states and
+    # words that no encoder writes: the oracle's verdict
+    lens = [1, 15, 63, 64, 65, 1023, 1024, 1025, 5000, 70_000]
+    vals = [0, 3, 77, 252, 255]
+    parts = [np.full(n, vals[i % 5], np.uint8) for i, n in enumerate(lens * 2)]
+    x = np.concatenate(parts)
+    col = zf.Column.compress(x, zf.ANS, chunk_elems=[len(p) for p in parts])
+    check([col], decode_image([col]), [x])
+    n = 1000
+    b = zo.encode(np.full(n, 77, np.uint8), zo.ANS)
+    c = zo.chunks(b)[0]
+    s0 = bytes(b[c["comp_off"]:c["comp_off"] + c["comp_len"]])
+    for lane, state, words in ((0, 65537, []), (63, 1, []), (7, 1, [0]), (7, 1, [1]), (5, 65536, [0]),
+                               (9, 1 << 31, []), (64, 0, [5] * 700)):
+        s = np.frombuffer(s0 + np.array(words, np.uint16).tobytes(), np.uint8).copy()
+        s[4:8] = np.frombuffer(np.uint32(len(words)).tobytes(), np.uint8)
+        for j in range(64):
+            if j == lane or lane == 64:
+                s[528 + 4 * j:532 + 4 * j] = np.frombuffer(np.uint32(state).tobytes(), np.uint8)
+        blob = H.container(zf.BYTES, [(s.tobytes(), n, zf.ANS)])
+        try:
+            want = zo.decode(blob)
+        except zo.OracleError:
+            want = None
+        try:
+            out, = decode_image([zf.Column.from_bytes(blob)])
+        except zf.ZfError as e:
+            assert e.status == zf.E_CORRUPT
+            out = None
+        log("ans of one byte: lane", lane, "state", state, len(words), "words:", "refused" if want is None else "taken")
+        assert (want is None) == (out is None)
+        assert want is None or np.array_equal(out, want)
