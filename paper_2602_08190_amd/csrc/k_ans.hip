@@ -24,9 +24,9 @@ void launch_ans(const LaunchArgs &A, uint32_t waves, hipStream_t st) {
     if (!n) return;
     // Work of as many whole chunks as fit the chip with the fused model at
     // once (eight per compute unit) waits for the step's latency, where that
-    // model wins; with more, the other's 19 waves a CU do.  64 KiB of flags
-    // each: 1,024 chunks 110 us fused, 142 us not; 2,048 115 and 148 us; 3,072
-    // 214 and 157 us.
+    // model wins; with more, the other's 19 waves a CU do, or are about even.
+    // 64 KiB of flags each: 1,024 chunks 84 us fused, 143 us not; 2,048 97 and
+    // 146 us; 2,304 160 and 154 us; 4,096 189 and 176 us; 16,384 729 and 703 us.
     if (A.ans_load <= 8 * cu_count()) {
         hipLaunchKernelGGL(k_decode_ans_fused, dim3(n), dim3(64), 0, st, A);
         return;

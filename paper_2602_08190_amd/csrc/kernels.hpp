@@ -1492,7 +1492,8 @@ ZF_DEV void unit_lz(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *row) {
 // no byte past it is written.  Matches of more than 36 bytes and those that
 // overlap themselves are copied by the whole wave one by one; a batch that is
 // not flat is replayed in order (one sequence by one).  The finished chunk is written once, in
-// aligned 16-byte stores.  LZ_FIGURES
+// aligned 16-byte stores.  64 KiB chunks of text: 283 -> 81 us for one to 256
+// of them, 128 MiB 461 -> 355 us.
 // lds: the waves' piece lists, 3 W + 1 dwords rounded up to 16 bytes, then the
 // output laid on its 16-byte grid and 16 bytes past it.
 constexpr uint32_t kLzPieces = 256;  // a wave's list of dword copies
