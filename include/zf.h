@@ -294,7 +294,9 @@ typedef struct {
 typedef struct {
     uint64_t slot_bytes;     /* staging slot size for transfers (default 256 MiB) */
     int32_t n_slots;         /* staging slots, >= 1 (default 2: double buffering)   */
-    int32_t use_graphs;      /* 1: one hipGraph per batch (default); 0: plain launches */
+    int32_t use_graphs;      /* 1: a hipGraph for each batch whose launches it
+                                speeds up, the many small ones (default);
+                                0: plain launches */
     int32_t persistent;      /* 1: a persistent multi-codec kernel per batch (two
                                 ordered launches when two-stage chunks are present),
                                 its waves pulling units from one queue per XCD;
@@ -410,7 +412,7 @@ typedef struct {
  * Transfer and decode (Sec. 3.3): for each batch in plan order, the copy
  * stream waits for its staging slot to be free, copies the batch's
  * compressed chunks from the columns' pinned memory over PCIe, and signals;
- * `stream` waits for that signal and runs the batch's decode graph.  With two
+ * `stream` waits for that signal and runs the batch's decode.  With two
  * slots the copy of batch k+1 overlaps the decode of batch k.  Outputs as in
  * zf_decompress_async.  `timing` (nullable) is filled by zf_sync.
  */

@@ -106,6 +106,12 @@ hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n,
     return hipGetLastError();
 }
 
+bool decode_forks(const LaunchArgs &A) {
+    auto count = [&](uint32_t k) { return A.kind_begin[k + 1] - A.kind_begin[k]; };
+    const uint32_t chain = count(K_LZ) + count(K_ANS), rest = A.kind_begin[K_COUNT] - chain - count(K_SDICT);
+    return chain && rest && A.ans_load <= 8 * cu_count() && A.lz_load <= 2 * cu_count();
+}
+
 // Enqueue the decode of one launch's units.  persistent_waves > 0 selects
 // the persistent kernel with that many waves in flight.  With `ev`, an event
 // is recorded on `st` before and after each kind's launch (slot K_COUNT: the
@@ -147,10 +153,8 @@ hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const u
     // after ANS, which writes its chunks' entry indices)
     static const uint32_t order[K_COUNT] = {K_LZ,     K_ANS,    K_SDICT,  K_RLE32,  K_RLE64, K_TREE, K_DICT128,
                                             K_DICT64, K_DICT32, K_FOR64, K_FOR32, K_F2I,   K_PLAIN};
-    auto count = [&](uint32_t k) { return A.kind_begin[k + 1] - A.kind_begin[k]; };
-    const uint32_t chain = count(K_LZ) + count(K_ANS), rest = A.kind_begin[K_COUNT] - chain - count(K_SDICT);
     const hipStream_t main = st;
-    const bool fork = side && !ev && chain && rest && A.ans_load <= 8 * cu_count() && A.lz_load <= 2 * cu_count();
+    const bool fork = side && side->stream && !ev && decode_forks(A);
     if (fork) {
         if ((e = hipEventRecord(side->fork, main)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return e;

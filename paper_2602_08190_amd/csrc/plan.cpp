@@ -580,13 +580,32 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     ZF_HIP(hipEventCreate(&P->ev_start));
     ZF_HIP(hipEventCreate(&P->ev_end));
     ZF_HIP(hipEventCreateWithFlags(&P->ev_dict, hipEventDisableTiming));
+    ZF_HIP(hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming));
     ZF_HIP(hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming));
 
-    if (o.use_graphs && !P->batches.empty()) {
+    // A batch of few launches goes without a graph, whose start costs the host
+    // 10 us and the device more than the launches' gaps.  One staged call, one
+    // batch of small columns, graph and launches: 1 kind 78 and 60 us, 3 kinds 80
+    // and 64 us, 6 kinds 83 and 77 us (but 61 and 77 us a call queued back to
+    // back), 13 kinds 131 and 134 us.  A batch whose kinds run beside each other
+    // (6 kinds of a 16-column table of 20,011 rows 175 and 158 us) always does.
+    auto as_graph = [&](const Batch &b) {
+        uint32_t kinds = 0;
+        for (uint32_t k = 0; k < K_COUNT; k++) kinds += b.args.kind_begin[k + 1] > b.args.kind_begin[k];
+        return o.use_graphs && (P->persistent_waves || (kinds > 5 && !decode_forks(b.args)));
+    };
+    bool any_graph = false, any_fork = false;
+    for (auto &b : P->batches) {
+        any_graph |= as_graph(b);
+        any_fork |= !as_graph(b) && !P->persistent_waves && decode_forks(b.args);
+    }
+    if (any_fork) ZF_HIP(hipStreamCreateWithFlags(&P->side_stream, hipStreamNonBlocking));
+    if (any_graph) {
         hipStream_t cap;
         ZF_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
         try {
             for (auto &b : P->batches) {
+                if (!as_graph(b)) continue;
                 ZF_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
                 hipError_t le = launch_decode(b.args, P->persistent_waves, b.w.wpb, P->lz_blk, cap);
                 hipError_t ce = hipStreamEndCapture(cap, &b.graph);
@@ -623,12 +642,13 @@ void release_plan(zf_plan_t *P) {
     kill(p.ev_h2d1);
     kill(p.ev_dec0);
     kill(p.ev_dec1);
-    for (auto e : {p.ev_start, p.ev_end, p.ev_dict, p.ev_join})
+    for (auto e : {p.ev_start, p.ev_end, p.ev_dict, p.ev_fork, p.ev_join})
         if (e) (void)hipEventDestroy(e);
     for (uint32_t k = 0; k <= K_COUNT; k++)
         for (auto e : {p.kind_ev.e0[k], p.kind_ev.e1[k]})
             if (e) (void)hipEventDestroy(e);
     if (p.copy_stream) (void)hipStreamDestroy(p.copy_stream);
+    if (p.side_stream) (void)hipStreamDestroy(p.side_stream);
     for (auto sp : p.d_slots)
         if (sp) (void)hipFree(sp);
     if (p.d_dict) (void)hipFree(p.d_dict);

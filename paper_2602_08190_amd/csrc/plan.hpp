@@ -10,6 +10,8 @@ namespace zf {
 // lz_blk: output bytes per block of the per-kind LZ77 kernel (4, 8 or 16).
 hipError_t launch_decode(const LaunchArgs &A, uint32_t persistent_waves, const uint32_t *waves_per_block,
                          uint32_t lz_blk, hipStream_t st, KindEvents *ev = nullptr, const SideStream *side = nullptr);
+// Would launch_decode use a second stream for this launch?
+bool decode_forks(const LaunchArgs &A);
 hipError_t launch_set_out_tab(uint8_t **d_tab, uint8_t *const *ptrs, uint32_t n, hipStream_t st);
 
 // One piece of a batch's transfer as the copy kernel takes it (device view of
@@ -90,9 +92,10 @@ struct zf_plan {
     std::vector<zf::Batch> batches; // in execution order
 
     hipStream_t copy_stream = nullptr;
+    hipStream_t side_stream = nullptr;  // beside a batch's decode (null: no batch forks)
     std::vector<hipEvent_t> slot_full, slot_free;
     std::vector<hipEvent_t> ev_h2d0, ev_h2d1, ev_dec0, ev_dec1;
-    hipEvent_t ev_start = nullptr, ev_end = nullptr, ev_dict = nullptr, ev_join = nullptr;
+    hipEvent_t ev_start = nullptr, ev_end = nullptr, ev_dict = nullptr, ev_fork = nullptr, ev_join = nullptr;
     zf_timing *pending_timing = nullptr;
     bool timing_valid = false;
     // per-kind events of profiled image decodes (zf_plan_profile)

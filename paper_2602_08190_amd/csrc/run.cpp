@@ -15,6 +15,16 @@ static void check_outputs(zf_plan_t *P, void *const *d_out) {
     }
 }
 
+// The output pointers travel with the launches; more columns than fit, and
+// graphs, read them in the device table, a launch of its own in every call
+// (10,007 values in one column: 10.5 us with it, 7 us without).
+static bool inline_outs(const zf_plan_t *P, void *const *d_out, LaunchArgs &A) {
+    A.inline_outs = P->cols.size() <= kInlineOuts;
+    if (A.inline_outs)
+        for (size_t c = 0; c < P->cols.size(); c++) A.outs[c] = static_cast<uint8_t *>(d_out[c]);
+    return A.inline_outs;
+}
+
 static void set_out_tab(zf_plan_t *P, void *const *d_out, hipStream_t st) {
     ZF_HIP(launch_set_out_tab(P->d_out_tab, reinterpret_cast<uint8_t *const *>(d_out), uint32_t(P->cols.size()), st));
 }
@@ -28,15 +38,8 @@ void decompress_async(zf_plan_t *P, const void *d_comp, uint64_t comp_bytes, voi
     LaunchArgs A = P->image_args;
     A.comp = static_cast<const uint8_t *>(d_comp);
     A.dict = static_cast<const uint8_t *>(d_comp);
-    // the output pointers travel with the launches; more columns than fit go
-    // through the device table, a launch of its own in every call (10,007
-    // values in one column: 10.5 us with it, 7 us without)
-    A.inline_outs = P->cols.size() <= kInlineOuts;
-    if (A.inline_outs)
-        for (size_t c = 0; c < P->cols.size(); c++) A.outs[c] = static_cast<uint8_t *>(d_out[c]);
-    else
-        set_out_tab(P, d_out, st);
-    const SideStream side{P->copy_stream, P->ev_dict, P->ev_join};
+    if (!inline_outs(P, d_out, A)) set_out_tab(P, d_out, st);
+    const SideStream side{P->copy_stream, P->ev_fork, P->ev_join};
     ZF_HIP(launch_decode(A, P->persistent_waves, P->image_wpb, P->lz_blk, st, P->profile ? &P->kind_ev : nullptr,
                          &side));
     if (P->profile) P->kinds_recorded = true;
@@ -45,12 +48,15 @@ void decompress_async(zf_plan_t *P, const void *d_comp, uint64_t comp_bytes, voi
 
 void transfer_and_decompress(zf_plan_t *P, void *const *d_out, hipStream_t st, zf_timing *timing) {
     check_outputs(P, d_out);
-    set_out_tab(P, d_out, st);
     // copies start after everything already queued on `st` (including the
     // previous call's decodes, which read the same slots)
     // (events that only measure are left out of a call that asks for no times)
     ZF_HIP(hipEventRecord(P->ev_start, st));
     ZF_HIP(hipStreamWaitEvent(P->copy_stream, P->ev_start, 0));
+    bool table = P->cols.size() > kInlineOuts;
+    for (const Batch &b : P->batches) table |= b.exec != nullptr;
+    if (table) set_out_tab(P, d_out, st);
+    const SideStream side{P->side_stream, P->ev_fork, P->ev_join};
     if (P->batches.empty() || !P->batches[0].n_pieces) {  // (else with the first batch)
         for (auto &cp : P->dict_copies)
             ZF_HIP(hipMemcpyAsync(P->d_dict + cp.dst_off, cp.src, cp.len, hipMemcpyHostToDevice, P->copy_stream));
@@ -74,8 +80,13 @@ void transfer_and_decompress(zf_plan_t *P, void *const *d_out, hipStream_t st, z
         ZF_HIP(hipEventRecord(P->slot_full[s], P->copy_stream));
         ZF_HIP(hipStreamWaitEvent(st, P->slot_full[s], 0));
         if (timing) ZF_HIP(hipEventRecord(P->ev_dec0[k], st));
-        if (b.exec) ZF_HIP(hipGraphLaunch(b.exec, st));
-        else ZF_HIP(launch_decode(b.args, P->persistent_waves, b.w.wpb, P->lz_blk, st));
+        if (b.exec) {
+            ZF_HIP(hipGraphLaunch(b.exec, st));
+        } else {
+            LaunchArgs A = b.args;
+            inline_outs(P, d_out, A);
+            ZF_HIP(launch_decode(A, P->persistent_waves, b.w.wpb, P->lz_blk, st, nullptr, &side));
+        }
         if (timing) ZF_HIP(hipEventRecord(P->ev_dec1[k], st));
         if (k + ns < P->batches.size()) ZF_HIP(hipEventRecord(P->slot_free[s], st));
     }

@@ -342,3 +342,35 @@ def test_ans_chunks_of_one_byte():
         log("ans of one byte: lane", lane, "state", state, len(words), "words:", "refused" if want is None else "taken")
         assert (want is None) == (out is None)
         assert want is None or np.array_equal(out, want)
+
+
+@pytest.mark.parametrize("copies", [1, 6])
+@pytest.mark.parametrize("kinds", ["few", "many", "chain"])
+def test_staged_launches(kinds, copies):
+    # batches of up to five launches go one by one, of more as a graph, those
+    # with a chain beside other kinds on two streams; output pointers of up to
+    # 32 columns with the launches; two sets of outputs in turn
+    n, r = 5_003, g.rng(copies)
+    make = [(zf.FOR_BP, lambda i: r.integers(0, 10 ** 6, size=n + i).astype(np.int32)),
+            (zf.RLE_DELTA_BP, lambda i: g.sorted_runs_column(n + i, 8, i)),
+            (zf.DICT_BP, lambda i: g.fixed16_column(n + i, 30, i))]
+    if kinds != "few":
+        make += [(zf.FOR_BP, lambda i: r.integers(0, 10 ** 6, size=n + i)),
+                 (zf.DICT_BP, lambda i: r.integers(0, 7, size=n + i)),
+                 (zf.RLE_DELTA_BP, lambda i: g.sorted_runs_column(n + i, 8, i, dtype=np.int64)),
+                 (zf.F2I_BP, lambda i: g.decimal_column(n + i, i, 100, 10 ** 6))]
+    if kinds == "chain":
+        make += [(zf.ANS, lambda i: g.text_column(n + i, i)), (zf.LZ77, lambda i: g.text_column(n + i, i))]
+    xs, cols = [], []
+    for i in range(copies):
+        for codec, m in make:
+            xs.append(m(i))
+            cols.append(zf.Column.compress(xs[-1], codec, pinned=True))
+    for slot in (1 << 16, 1 << 24):
+        plan = zf.Plan(cols, slot_bytes=slot)
+        a, b = zf.empty_outputs(cols), zf.empty_outputs(cols)
+        for outs in (a, b, a):
+            plan.transfer_and_decompress(outs, timing=False)
+        plan.sync()
+        check(cols, [o.cpu().numpy() for o in a], xs)
+        check(cols, [o.cpu().numpy() for o in b], xs)
