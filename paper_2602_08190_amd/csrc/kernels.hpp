@@ -783,21 +783,33 @@ ZF_DEV uint32_t scan_lengths(uint32_t r, uint32_t last, uint64_t &total) {
 // progression with the run's stride, a progression with one stride for all.
 enum class Run { kConst, kStride, kOneStride };
 
-// Expansion of one group of up to 64 runs into out[a, bnd): lane j holds run
-// j (act), which starts at start_abs, and its value: v (kConst), or v + dstr *
-// p at element p.  Output goes by spans of 2048 elements.  Every run that
-// starts in the span sets its bit in a map of 64 words, one per lane, so that
-// an element's run is the runs that start before the span, plus the set bits
-// up to the element: a count per word from one scan, and the bits of the
-// element's own word.  Each lane then takes 16 bytes of output, its values
-// fetched from their runs with cross-lane permutes: no per-run loop, and the
-// same work whatever the run lengths.  map: this wave's 64 dwords.
-// 33.6 M int32 in runs of 8 (3): 45.6 (73) us with a slot per element and a
-// carry from window to window, 37.0 (58) us so; order keys 58.6 and 46.1.
-template <class U, Run RUN>
-ZF_DEV void expand_runs(U *out, uint32_t a, uint32_t bnd, bool act, uint32_t start_abs, U v, U dstr, uint32_t *map) {
-    constexpr uint32_t R = 16 / sizeof(U), WIN = 64 * R, SPAN = 2048;
-    if (a >= bnd) return;
+// Expansion of one group of up to 64 runs into the part of a unit's output
+// out[e0, e1) that lies in [goff, next_off): lane j holds run j (act), which
+// starts at start_abs, and its value: v (kConst), or v + dstr * p at element p.
+// Output goes by spans of 2048 elements.  Every run that starts in the span
+// sets its bit in a map of 64 words, one per lane, so that an element's run is
+// the runs that start before the span, plus the set bits up to the element: a
+// count per word from one scan, and the bits of the element's own word.  Each
+// lane then takes 16 bytes of output, its values fetched from their runs with
+// cross-lane permutes: no per-run loop, and the same work whatever the run
+// lengths.  map: this wave's 64 dwords.
+// A span goes by windows of 1 KiB.  A line of output written in parts past the
+// caches costs several times a whole one, so with CARRY the windows lie on the
+// output's 128-byte grid, counted from the unit's start, and one that a group
+// leaves unfinished is carried to the next (open: this lane's values in it);
+// only the unit's ends write parts of lines, through the caches.  Else the
+// windows begin with the group, on the 16-byte grid, which is a window fewer
+// for most groups.
+template <class U>
+struct Window {
+    U val[16 / sizeof(U)];
+};
+template <class U, Run RUN, bool CARRY = false>
+ZF_DEV void expand_runs(U *out, uint32_t e0, uint32_t e1, uint32_t goff, uint32_t next_off, bool act,
+                        uint32_t start_abs, U v, U dstr, uint32_t *map, Window<U> &open) {
+    constexpr int32_t R = 16 / sizeof(U), WIN = 64 * R, SPAN = 2048, LINE = 128 / sizeof(U);
+    const int32_t ua = int32_t(e0), ub = int32_t(e1), ia = int32_t(max(e0, goff)), ib = int32_t(min(e1, next_off));
+    if (ia >= ib) return;
     const uint32_t lane = lane_id();
     auto fetch = [&](int src, U x) -> U {
         if constexpr (sizeof(U) == 4) {
@@ -808,46 +820,62 @@ ZF_DEV void expand_runs(U *out, uint32_t a, uint32_t bnd, bool act, uint32_t sta
             return uint64_t(lo) | (uint64_t(hi) << 32);
         }
     };
-    // spans on the output's 16-byte grid (signed: the first may start before
-    // element 0)
-    const int32_t mis = int32_t((reinterpret_cast<uintptr_t>(out + a) & 15u) / sizeof(U));
-    const int32_t ia = int32_t(a), ib = int32_t(bnd);
+    // (signed: the first window may start before element 0)
+    const int32_t lo = CARRY ? ua : ia;
+    const int32_t w0 = lo - int32_t((reinterpret_cast<uintptr_t>(out + lo) & (CARRY ? 127u : 15u)) / sizeof(U));
     const uint32_t sh = (R * lane) & 31u, upto = (2u << sh) - 1u;  // bits up to the lane's first element's
-    for (int32_t S = ia - mis; S < ib; S += int32_t(SPAN)) {
+    for (int32_t S = w0 + (ia - w0) / WIN * WIN; S < ib; S += SPAN) {
         map[lane] = 0;
         wave_fence();
         const uint32_t rel = start_abs - uint32_t(S);
-        if (act && rel < SPAN)
+        if (act && rel < uint32_t(SPAN))
             __hip_atomic_fetch_or(map + (rel >> 5), 1u << (rel & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         wave_fence();
         const uint32_t bits = map[lane], c = uint32_t(__popc(bits));
         // runs that start before this lane's word, less one
         const uint32_t before = scan_add32(c) - c + uint32_t(__popcll(__ballot(act && int32_t(start_abs) < S))) - 1u;
         wave_fence();
-        const int32_t E = min(S + int32_t(SPAN), ib);
-        for (int32_t W = S; W < E; W += int32_t(WIN)) {
+        const int32_t E = min(S + SPAN, ib);
+        for (int32_t W = S; W < E; W += WIN) {
             const int word = int(uint32_t(W - S) / 8 + ((R * lane) >> 5) * 4);  // (4 x the word's lane)
             const uint32_t b = uint32_t(__builtin_amdgcn_ds_bpermute(word, int(bits)));
             uint32_t run = uint32_t(__builtin_amdgcn_ds_bpermute(word, int(before))) + uint32_t(__popc(b & upto));
-            const int32_t p = W + int32_t(R * lane);
+            const int32_t p = W + R * int32_t(lane);
             U val[R];
 #pragma unroll
-            for (uint32_t i = 0; i < R; i++) {
+            for (int32_t i = 0; i < R; i++) {
                 if (i) run += (b >> (sh + i)) & 1u;
                 const int src = int(run * 4);
                 val[i] = fetch(src, v);
-                if constexpr (RUN == Run::kStride) val[i] = U(val[i] + fetch(src, dstr) * U(uint32_t(p + int32_t(i))));
-                if constexpr (RUN == Run::kOneStride) val[i] = U(val[i] + dstr * U(uint32_t(p + int32_t(i))));
+                if constexpr (RUN == Run::kStride) val[i] = U(val[i] + fetch(src, dstr) * U(uint32_t(p + i)));
+                if constexpr (RUN == Run::kOneStride) val[i] = U(val[i] + dstr * U(uint32_t(p + i)));
             }
-            if (p >= ia && p + int32_t(R) <= ib) {
-                u32x4 q;
-                if constexpr (sizeof(U) == 4) q = u32x4{val[0], val[1], val[2], val[3]};
-                else q = u32x4{uint32_t(val[0]), uint32_t(val[0] >> 32), uint32_t(val[1]), uint32_t(val[1] >> 32)};
-                __builtin_nontemporal_store(q, gp(reinterpret_cast<u32x4 *>(out + p)));
+            if (CARRY && W < ia) {  // (its elements before ia are the groups' before this one)
+#pragma unroll
+                for (int32_t i = 0; i < R; i++) val[i] = p + i < ia ? open.val[i] : val[i];
+            }
+            u32x4 q;
+            if constexpr (sizeof(U) == 4) q = u32x4{val[0], val[1], val[2], val[3]};
+            else q = u32x4{uint32_t(val[0]), uint32_t(val[0] >> 32), uint32_t(val[1]), uint32_t(val[1] >> 32)};
+            ZF_GLOBAL u32x4 *at = gp(reinterpret_cast<u32x4 *>(out + p));
+            auto parts = [&]() {
+#pragma unroll
+                for (int32_t i = 0; i < R; i++)
+                    if (p + i >= lo && p + i < ib) gp(out)[p + i] = val[i];
+            };
+            if constexpr (!CARRY) {
+                if (p >= lo && p + R <= ib) __builtin_nontemporal_store(q, at);
+                else parts();
+            } else if (W >= lo && W + WIN <= ib) {
+                __builtin_nontemporal_store(q, at);
+            } else if (W + WIN <= ib || ib == ub) {
+                const int32_t l = p - ((R * int32_t(lane)) & (LINE - 1));  // its line's first element
+                if (l >= lo && l + LINE <= ib) __builtin_nontemporal_store(q, at);
+                else if (p >= lo && p + R <= ib) *at = q;
+                else parts();
             } else {
 #pragma unroll
-                for (int32_t i = 0; i < int32_t(R); i++)
-                    if (p + i >= ia && p + i < ib) gp(out)[p + i] = val[i];
+                for (int32_t i = 0; i < R; i++) open.val[i] = val[i];
             }
         }
     }
@@ -880,7 +908,7 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len, lane = lane_id();
     const bool unit_runs = ck.codec == C_DELTA_BP;
-    U *out = reinterpret_cast<U *>(out_of(A, ck) + ck.out_off);
+    U *out = reinterpret_cast<U *>(uniform_ptr(out_of(A, ck) + ck.out_off));
     if (clen < 16) {
         flag(A.err, ERR_CORRUPT);
         return;
@@ -969,56 +997,73 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
             }
         }
     }
-    Group cur, nxt;
-    load(t.a, cur);
-    for (uint32_t g = t.a;; g++) {
-        if (!cur.ok || (g == t.a && cur.goff > e0)) {
-            flag(A.err, ERR_CORRUPT);
-            return;
-        }
-        const bool more = cur.next_off < e1;
-        if (more) {
-            if (g + 1 >= ng) {
+    auto groups = [&](auto carried) {
+        constexpr bool CARRY = decltype(carried)::value;
+        Group cur, nxt;
+        Window<U> open{};
+        load(t.a, cur);
+        for (uint32_t g = t.a;; g++) {
+            if (!cur.ok || (g == t.a && cur.goff > e0)) {
                 flag(A.err, ERR_CORRUPT);
                 return;
             }
-            if (!rec.has(g)) rec.load<32>(s + 16, g, ng);
-            load(g + 1, nxt);  // in flight while this group is expanded
+            const bool more = cur.next_off < e1;
+            if (more) {
+                if (g + 1 >= ng) {
+                    flag(A.err, ERR_CORRUPT);
+                    return;
+                }
+                if (!rec.has(g)) rec.load<32>(s + 16, g, ng);
+                load(g + 1, nxt);  // in flight while this group is expanded
+            }
+            // run lengths -> output offsets (exclusive scan = presum)
+            const bool act = lane < cur.cnt;
+            const uint32_t r = act ? cur.r : 0u;
+            uint64_t total;
+            const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
+            if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
+                flag(A.err, ERR_CORRUPT);
+                return;
+            }
+            const uint32_t start_abs = cur.goff + incl - r;  // start of run `lane`
+            // RLE: run values are base, then base + prefix sums of (dmin + field).
+            // DeltaStride: run j writes c_j + d_j * p at element p, with stride
+            // d_j = dmin + field, start s_j = s_{j-1} + d_{j-1} r_{j-1} + gap_j
+            // (gap_j = gmin + field, s_0 = base) and c_j = s_j - d_j * start_j.
+            const U field = field_from<U>(cur.f, lane - 1, cur.w);  // (lane 0's is not used)
+            U v, dstr = 0;
+            if constexpr (DS) {
+                dstr = act ? U(cur.dmin + field_from<U>(cur.d, lane, cur.wd)) : U(0);
+                // start_j = base + sum_{k<j} stride_k count_k + sum_{k<=j} gap_k:
+                // an exclusive and an inclusive wave scan, no cross-lane reads
+                const U f = act ? U(dstr * U(r)) : U(0);
+                const U gap = act && lane >= 1 ? U(cur.gmin + field) : U(0);
+                const U F = scan_addT<U>(f), Gs = scan_addT<U>(gap);
+                const U st = U(cur.base + (F - f) + Gs);
+                v = U(st - dstr * U(start_abs));
+            } else {
+                const U delta = lane ? U(cur.dmin + field) : cur.base;
+                v = scan_addT<U>(act ? delta : U(0));
+            }
+            expand_runs<U, DS ? Run::kStride : Run::kConst, CARRY>(out, e0, e1, cur.goff, cur.next_off, act, start_abs,
+                                                                   v, dstr, map, open);
+            if (!more) return;
+            cur = nxt;
         }
-        // run lengths -> output offsets (exclusive scan = presum)
-        const bool act = lane < cur.cnt;
-        const uint32_t r = act ? cur.r : 0u;
-        uint64_t total;
-        const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
-        if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
-            flag(A.err, ERR_CORRUPT);
+    };
+    // Windows are carried where a run is 36 bytes or more on average.  30 M int32
+    // (units of 1024) in runs of 4, 6, 8, 12, 100, carried and not: 48.7, 38.6,
+    // 33.5, 27.2, 24.5 and 47.2, 37.7, 34.3, 34.9, 32.7 us (120 M in runs of 100: 80
+    // and 121); int64 (units of 512) in runs of 4, 5, 8, 100: 62.6, 54.6, 47.8, 44.1
+    // and 60.5, 59.8, 62.5, 59.8 us.  (DeltaStride, with a longer chain per window,
+    // only loses by it.)
+    if constexpr (!DS) {
+        if (uint64_t(n) * sizeof(U) >= 36ull * nr) {
+            groups(std::true_type{});
             return;
         }
-        const uint32_t start_abs = cur.goff + incl - r;  // start of run `lane`
-        // RLE: run values are base, then base + prefix sums of (dmin + field).
-        // DeltaStride: run j writes c_j + d_j * p at element p, with stride
-        // d_j = dmin + field, start s_j = s_{j-1} + d_{j-1} r_{j-1} + gap_j
-        // (gap_j = gmin + field, s_0 = base) and c_j = s_j - d_j * start_j.
-        const U field = field_from<U>(cur.f, lane - 1, cur.w);  // (lane 0's is not used)
-        U v, dstr = 0;
-        if constexpr (DS) {
-            dstr = act ? U(cur.dmin + field_from<U>(cur.d, lane, cur.wd)) : U(0);
-            // start_j = base + sum_{k<j} stride_k count_k + sum_{k<=j} gap_k:
-            // an exclusive and an inclusive wave scan, no cross-lane reads
-            const U f = act ? U(dstr * U(r)) : U(0);
-            const U gap = act && lane >= 1 ? U(cur.gmin + field) : U(0);
-            const U F = scan_addT<U>(f), Gs = scan_addT<U>(gap);
-            const U st = U(cur.base + (F - f) + Gs);
-            v = U(st - dstr * U(start_abs));
-        } else {
-            const U delta = lane ? U(cur.dmin + field) : cur.base;
-            v = scan_addT<U>(act ? delta : U(0));
-        }
-        expand_runs<U, DS ? Run::kStride : Run::kConst>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs,
-                                                         v, dstr, map);
-        if (!more) return;
-        cur = nxt;
     }
+    groups(std::false_type{});
 }
 
 // ============================= DeltaStride | [Delta | RLE | [BP, BP], BP]
@@ -1032,7 +1077,7 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
 // read their groups' records and the next group's words ahead, as unit_rle.
 
 // First stage: S[t.b, t.c) of a chunk (ck.n_elems = R starts, written at
-// out_tab[kScratchCol] + ck.out_off), starting with D's group t.a.
+// ck.out_off of the scratch area), starting with D's group t.a.
 template <class U>
 ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uint32_t *map) {
     constexpr uint32_t BITS = sizeof(U) * 8;
@@ -1079,6 +1124,7 @@ ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc
         G.l = field_words<uint32_t>(s, poff + 4 * vw, poff + 4 * (vw + lw), lane, G.wl);
     };
     Group cur, nxt;
+    Window<U> open{};
     load(t.a, cur);
     for (uint32_t g = t.a;; g++) {
         if (!cur.ok || (g == t.a && cur.goff > e0)) {
@@ -1109,7 +1155,7 @@ ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc
         const U F = scan_addT<U>(f);
         const U first = U(cur.base + (F - f) + vj);
         const U c = U(first - vj * U(start_abs));
-        expand_runs<U, Run::kStride>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs, c, vj, map);
+        expand_runs<U, Run::kStride>(out, e0, e1, cur.goff, cur.next_off, act, start_abs, c, vj, map, open);
         if (!more) return;
         cur = nxt;
     }
@@ -1160,6 +1206,7 @@ ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, u
         if (G.ok) G.c = field_words<uint32_t>(s, poff, poff + 4 * cw, lane, G.wc);
     };
     Group cur, nxt;
+    Window<U> open{};
     load(t.a, cur);
     for (uint32_t g = t.a;; g++) {
         if (!cur.ok || (g == t.a && cur.goff > e0)) {
@@ -1185,7 +1232,7 @@ ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, u
         }
         const uint32_t start_abs = cur.goff + incl - r;
         const U c = U(cur.st - d * U(start_abs));
-        expand_runs<U, Run::kOneStride>(out, max(e0, cur.goff), min(e1, cur.next_off), act, start_abs, c, d, map);
+        expand_runs<U, Run::kOneStride>(out, e0, e1, cur.goff, cur.next_off, act, start_abs, c, d, map, open);
         if (!more) return;
         cur = nxt;
     }

@@ -374,3 +374,24 @@ def test_staged_launches(kinds, copies):
         plan.sync()
         check(cols, [o.cpu().numpy() for o in a], xs)
         check(cols, [o.cpu().numpy() for o in b], xs)
+
+
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("run", [1, 4, 5, 8, 9, 40, 700, 5000])
+def test_carried_windows(dtype, run):
+    # run lengths on both sides of the carrying rule (36 bytes a run), units
+    # that cut groups, chunks of odd lengths off the 128-byte grid, chunks
+    # shorter than a window; outputs not a multiple of a line long
+    r = g.rng(run)
+    for unit in (64, 500, 4096):
+        xs, cols = [], []
+        for n in (1, 31, 257, 1023, 12_345, 70_001):
+            lens = r.integers(1, 2 * run, size=n // run + 2) if run > 1 else r.integers(1, 3, size=n + 2)
+            x = np.repeat(r.integers(-2 ** 31, 2 ** 31, size=len(lens)), lens).astype(dtype)[:n]
+            xs.append(x)
+            n = len(x)
+            ce = None if n < 2000 else [777, 1, n // 2, n - n // 2 - 778]
+            cols.append(zf.Column.compress(x, zf.RLE_DELTA_BP, chunk_elems=ce))
+        tiles = {k: dict(unit=unit, waves_per_block=4) for k in ("RLE32", "RLE64")}
+        check(cols, decode_image(cols, tiles=tiles), xs)
+        check(cols, decode_image(cols, persistent=True, tiles=tiles), xs)
