@@ -203,7 +203,8 @@ struct KindLoad {
 // Shapes the caller set stay.  Units of 256 elements, 1,024 bytes of tokens,
 // one block and 8 KiB of plain copy are the smallest: smaller ones were no
 // faster.  The DSTREE output, which the cache does not hold, takes units of at
-// most 512 (33.6 M int64 keys 84 -> 71 us, int32 46 us with any).  Measured,
+// most 512 (30 M int64 keys 47 us, 51 with 1,024 and 56 with 4,096; 33.6 M int32
+// 35, 36 and 44 us).  Measured,
 // with the cache's shape and this rule's:
 //   String-dictionary, 1.5 MB 81 -> 10.5 us, 16 MiB 83 -> 20, 64 MiB 86 -> 46
 //   DSTREE output, 3 M keys 25 -> 10 us; RLE32, 300,000 dates 10.2 -> 7.0

@@ -395,3 +395,28 @@ def test_carried_windows(dtype, run):
         tiles = {k: dict(unit=unit, waves_per_block=4) for k in ("RLE32", "RLE64")}
         check(cols, decode_image(cols, tiles=tiles), xs)
         check(cols, decode_image(cols, persistent=True, tiles=tiles), xs)
+
+
+@pytest.mark.parametrize("run", [1, 3, 4, 5, 8, 40, 700])
+def test_carried_windows_of_progressions(run):
+    # DeltaStride and its tree on both sides of the carrying rule, int64 and
+    # int32, units that cut groups, chunks off the 128-byte grid
+    r = g.rng(100 + run)
+    for dtype in (np.int32, np.int64):
+        xs, cols = [], []
+        for n in (1, 33, 1023, 20_011):
+            parts, at = [], 0
+            while sum(map(len, parts)) < n:
+                k = int(r.integers(1, 2 * run)) if run > 1 else 1
+                at += int(r.integers(1, 50))
+                parts.append(at + np.arange(k))
+                at += k
+            x = np.concatenate(parts)[:n].astype(dtype)
+            for codec in (zf.DSTRIDE_BP, zf.DSTREE):
+                xs.append(x)
+                ce = None if n < 2000 else [777, 1, n // 2, n - n // 2 - 778]
+                cols.append(zf.Column.compress(x, codec, chunk_elems=ce))
+        for unit in (64, 500, 4096):
+            tiles = {k: dict(unit=unit, waves_per_block=4) for k in ("RLE32", "RLE64", "TREE")}
+            check(cols, decode_image(cols, tiles=tiles), xs)
+            check(cols, decode_image(cols, persistent=True, tiles=tiles), xs)
