@@ -63,10 +63,6 @@ ZF_DEV T *uniform_ptr(T *p) {
     return reinterpret_cast<T *>(u);
 }
 
-// The lanes on which p holds.  (A comparison's own lane mask; of anything else,
-// such as two of them, the compiler makes a select and a second comparison.)
-ZF_DEV uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
 // Inclusive prefix sums across the 64 lanes (wrapping), with DPP lane moves:
 // row_shr 1, 2, 4, 8 inside each row of 16 lanes, then row_bcast 15 and 31
 // carry the row totals into the rows above (GCN / CDNA DPP controls).
@@ -111,7 +107,7 @@ ZF_DEV T scan_addT(T x) {
 // with a nonzero x (unchanged if there is none).  A ballot finds the lane,
 // one cross-lane read fetches its x.
 ZF_DEV uint32_t last_nonzero_below(uint32_t x, uint32_t &carry) {
-    const uint64_t m = ballot(x != 0);
+    const uint64_t m = __ballot(x != 0);
     const uint64_t b = m & ((uint64_t(1) << __lane_id()) - 1);
     const uint32_t hi = uint32_t(b >> 32), lo = uint32_t(b);
     const uint32_t src = hi ? 63u - uint32_t(__clz(int(hi))) : 31u - uint32_t(__clz(int(lo)));
@@ -126,7 +122,7 @@ ZF_DEV uint32_t wave_max32(uint32_t x) {
     for (int d = 32; d >= 1; d >>= 1) x = max(x, uint32_t(__shfl_xor(x, d, 64)));
     return x;
 }
-ZF_DEV bool any(bool p) { return ballot(p) != 0; }
+ZF_DEV bool any(bool p) { return __ballot(p) != 0; }
 
 // Orders this wave's global memory accesses for the compiler.  Lanes of one
 // wavefront share one in-order path to the L1, so a load issued after a
@@ -837,7 +833,7 @@ ZF_DEV void expand_runs(U *out, uint32_t e0, uint32_t e1, uint32_t goff, uint32_
         wave_fence();
         const uint32_t bits = map[lane], c = uint32_t(__popc(bits));
         // runs that start before this lane's word, less one
-        const uint32_t before = scan_add32(c) - c + uint32_t(__popcll(ballot(act) & ballot(int32_t(start_abs) < S))) - 1u;
+        const uint32_t before = scan_add32(c) - c + uint32_t(__popcll(__ballot(act && int32_t(start_abs) < S))) - 1u;
         wave_fence();
         const int32_t E = min(S + SPAN, ib);
         for (int32_t W = S; W < E; W += WIN) {
@@ -1029,7 +1025,7 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
             const uint32_t r = act ? cur.r : 0u;
             uint64_t total;
             const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
-            if ((ballot(act) & ballot(r == 0)) || uint64_t(cur.goff) + total != cur.next_off) {
+            if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
                 flag(A.err, ERR_CORRUPT);
                 return;
             }
@@ -1154,7 +1150,7 @@ ZF_DEV void unit_tree_starts(const LaunchArgs &A, const Tile &t, const ChunkDesc
         const uint32_t r = act ? cur.lmin + field_from<uint32_t>(cur.l, lane, cur.wl) : 0u;
         uint64_t total;
         const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
-        if ((ballot(act) & ballot(r == 0)) || uint64_t(cur.goff) + total != cur.next_off) {
+        if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
@@ -1238,7 +1234,7 @@ ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, u
         const uint32_t r = act ? cur.cmin + field_from<uint32_t>(cur.c, lane, cur.wc) : 0u;
         uint64_t total;
         const uint32_t incl = scan_lengths(r, cur.cnt - 1, total);
-        if ((ballot(act) & ballot(r == 0)) || uint64_t(cur.goff) + total != cur.next_off) {
+        if (any(act && r == 0) || uint64_t(cur.goff) + total != cur.next_off) {
             flag(A.err, ERR_CORRUPT);
             return;
         }
@@ -1609,7 +1605,7 @@ ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
     // the batch's count of extension words goes to the other waves; the
     // lane's own number within the batch
     auto count_ext = [&](uint32_t t) {
-        const uint64_t b7 = ballot((t & 7u) == 7u), b31 = ballot((t >> 3) == 31u);
+        const uint64_t b7 = __ballot((t & 7u) == 7u), b31 = __ballot((t >> 3) == 31u);
         if (lane == 0) n_ext[w] = uint32_t(__popcll(b7) + __popcll(b31));
         return __builtin_amdgcn_mbcnt_hi(uint32_t(b7 >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(b7), 0u)) +
                __builtin_amdgcn_mbcnt_hi(uint32_t(b31 >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(b31), 0u));
@@ -1717,7 +1713,7 @@ ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
                     if (any(m >= 4 && m > 4 * i) && m >= 4 && m > 4 * i)
                         __builtin_memcpy(ob + P + min(4 * i, m - 4), &v[i], 4);
             }
-            for (uint64_t b = ballot(ll > 32); b; b &= b - 1) {
+            for (uint64_t b = __ballot(ll > 32); b; b &= b - 1) {
                 const uint32_t k = uint32_t(__builtin_ctzll(b)), Pk = rl32(P, k), Lk = rl32(LP, k), lk = rl32(ll, k);
                 for (uint32_t j = lane; j < lk; j += 64) ob[Pk + j] = lits[Lk + j];
             }
@@ -1736,7 +1732,7 @@ ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
         // the lanes take equal shares
         uint32_t m = flat && ml <= 36 && off >= ml ? ml : 0u;  // (at least 4 if any)
         const uint32_t pincl2 = scan_add32((m + 3) >> 2), at = pincl2 - ((m + 3) >> 2);
-        const uint64_t fits = ballot(pincl2 <= kLzPieces);  // (the first lanes)
+        const uint64_t fits = __ballot(pincl2 <= kLzPieces);  // (the first lanes)
         if (pincl2 > kLzPieces) m = 0;
         const uint32_t pieces = fits ? rl32(pincl2, uint32_t(__popcll(fits)) - 1) : 0u;
 #pragma unroll
@@ -1761,7 +1757,7 @@ ZF_DEV void chunk_lz(const LaunchArgs &A, const ChunkDesc &ck, uint8_t *lds) {
 #pragma unroll
                 for (uint32_t i = 0; i < kLzPieces / 64; i++)
                     if (64 * i < pieces && 64 * i + lane < pieces) __builtin_memcpy(ob + (piece[i] >> 16), &x[i], 4);
-                for (uint64_t b = ballot(ml != 0 && m == 0); b; b &= b - 1) {
+                for (uint64_t b = __ballot(ml != 0 && m == 0); b; b &= b - 1) {
                     const uint32_t k = uint32_t(__builtin_ctzll(b));
                     copy_long(rl32(D, k), rl32(q0, k), rl32(ml, k), rl32(off, k));
                 }
@@ -2415,7 +2411,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     // a chunk of one byte, as an encoder writes it (otherwise its states, which
     // stand still, are followed step by step)
     const uint64_t single =
-        FUSED ? ballot(f[0] == kAnsM || f[1] == kAnsM || f[2] == kAnsM || f[3] == kAnsM) : 0ull;
+        FUSED ? __ballot(f[0] == kAnsM || f[1] == kAnsM || f[2] == kAnsM || f[3] == kAnsM) : 0ull;
     if (single && nw == 0 && !any(x != kAnsL)) {
         const uint32_t b = rl32(4 * lane + (f[1] ? 1 : 0) + (f[2] ? 2 : 0) + (f[3] ? 3 : 0),
                                 uint32_t(__builtin_ctzll(single)));
@@ -2513,7 +2509,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
             const uint32_t xn = fx * (xs & 0xFFFFFFu) + ((b >> 8) & 0xFFFu);
             __builtin_amdgcn_sched_barrier(0);
             const bool need = act && xn < kAnsL;  // one word at most: x >= 1 * 2^4 before the shift
-            const uint64_t m = ballot(need);
+            const uint64_t m = __ballot(need);
             __builtin_amdgcn_sched_barrier(0);
             uint32_t a = (xn << 2) & 0x3FFCu;
             asm volatile("" : "+v"(a));
@@ -2543,7 +2539,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
             const uint32_t xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
             x = act ? xn : x;
             const bool need = act && x < kAnsL;
-            const uint64_t m = ballot(need);
+            const uint64_t m = __ballot(need);
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
             const uint32_t p0 = pos & (kAnsRing - 1);
             const uint32_t w = reinterpret_cast<const uint16_t *>(ring)[p0 + rank];
