@@ -792,7 +792,8 @@ enum class Run { kConst, kStride, kOneStride };
 // count per word from one scan, and the bits of the element's own word.  Each
 // lane then takes 16 bytes of output, its values fetched from their runs with
 // cross-lane permutes: no per-run loop, and the same work whatever the run
-// lengths.  map: this wave's 64 dwords.
+// lengths.  map: this wave's 64 dwords.  33.6 M int32 in runs of 8 (3): 45.6 (73)
+// us with a slot per element and a carry from window to window, 37 (60) us so.
 // A span goes by windows of 1 KiB.  A line of output written in parts past the
 // caches costs several times a whole one, so with CARRY the windows lie on the
 // output's 128-byte grid, counted from the unit's start, and one that a group
@@ -1055,15 +1056,15 @@ ZF_DEV void unit_rle(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, ui
             cur = nxt;
         }
     };
-    // Windows are carried where a run is 36 bytes or more on average.  30 M int32
-    // (units of 1024) in runs of 4, 6, 8, 12, 100, carried and not: 48.7, 38.6,
-    // 33.5, 27.2, 24.5 and 47.2, 37.7, 34.3, 34.9, 32.7 us (120 M in runs of 100: 80
-    // and 121); int64 (units of 512) in runs of 4, 5, 8, 100: 62.6, 54.6, 47.8, 44.1
-    // and 60.5, 59.8, 62.5, 59.8 us.  DeltaStride, with a longer chain per window,
-    // gains where a line holds 16 values: 30 M int64 keys 64 -> 54 us, int32 40 ->
-    // 42.
+    // Windows are carried where a run is 5 elements or more on average.  30 M
+    // int32 (units of 2048) in runs of 4, 5, 8, 12, 100, carried and not: 47.6,
+    // 41.0, 31.6, 29.6, 28 and 46.7, 42.3, 38.9, 37.5, 34 us (the fact table's
+    // dates 0.120 and 0.155 ms); int64 (units of 512) in runs of 4, 5, 8, 100: 62.6,
+    // 54.6, 47.8, 44.1 and 60.5, 59.8, 62.5, 59.8 us.  DeltaStride, with a longer
+    // chain per window, gains where a line holds 16 values: 30 M int64 keys 64 -> 54
+    // us, int32 40 -> 42.
     if constexpr (!DS || sizeof(U) == 8) {
-        if (uint64_t(n) * sizeof(U) >= 36ull * nr) {
+        if (n / 5 >= nr) {
             groups(std::true_type{});
             return;
         }
@@ -1241,7 +1242,7 @@ ZF_DEV void unit_tree(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, u
         const uint32_t start_abs = cur.goff + incl - r;
         const U c = U(cur.st - d * U(start_abs));
         // (carried as in unit_rle: 30 M int64 keys 62 -> 47 us, 33.6 M int32 35 -> 38)
-        if (sizeof(U) == 8 && uint64_t(n) * sizeof(U) >= 36ull * R)
+        if (sizeof(U) == 8 && n / 5 >= R)
             expand_runs<U, Run::kOneStride, sizeof(U) == 8>(out, e0, e1, cur.goff, cur.next_off, act, start_abs, c, d,
                                                             map, open);
         else
@@ -1425,7 +1426,7 @@ ZF_DEV void unit_lz(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *row) {
     const uint32_t clen = ck.comp_len, lane = lane_id();
     const uint32_t es = ck.dtype == D_I32 ? 4 : ck.dtype == D_I64 ? 8 : ck.dtype == D_FIXED16 ? 16 : 1;
     const uint32_t plain = ck.n_elems * es;
-    uint8_t *out = out_of(A, ck) + ck.out_off;
+    uint8_t *out = uniform_ptr(out_of(A, ck) + ck.out_off);
     if (clen < 16) {
         flag(A.err, ERR_CORRUPT);
         return;
