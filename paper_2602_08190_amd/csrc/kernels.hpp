@@ -2416,9 +2416,10 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     if (single && nw == 0 && !any(x != kAnsL)) {
         const uint32_t b = rl32(4 * lane + (f[1] ? 1 : 0) + (f[2] ? 2 : 0) + (f[3] ? 3 : 0),
                                 uint32_t(__builtin_ctzll(single)));
-        const uint32_t v = b * 0x01010101u, m = (reinterpret_cast<uintptr_t>(out) & 15u) == 0 ? n & ~15u : 0u;
-        for (uint32_t i = 16 * lane; i < m; i += 16 * 64) st16_nt(out + i, v, v, v, v);
-        for (uint32_t i = m + lane; i < n; i += 64) gp(out)[i] = uint8_t(b);
+        const uint32_t v = b * 0x01010101u;
+        fill_lane(
+            n, (reinterpret_cast<uintptr_t>(out) & 15u) == 0, lane,
+            [&](uint32_t i) { st16_nt(out + i, v, v, v, v); }, [&](uint32_t i) { gp(out)[i] = uint8_t(b); });
         return;
     }
     uint32_t *tab = lds;                                                  // FUSED: slot -> entry
@@ -2552,7 +2553,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         }
     };
     bool bad = false;
-    const uint32_t steps = (n + kAnsLanes - 1) / kAnsLanes;
+    const uint32_t steps = rounds_of(n, kAnsLanes);
     // entry indices, which the String-dictionary launch reads next, stay in the
     // caches (512 MiB of text: that launch 338 -> 264 us)
     const bool again = ck.col == kScratchCol;

@@ -24,6 +24,18 @@ constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 40
 // String-dictionary: longest token
 constexpr uint32_t kSdMaxToken = 64;
 
+// Rounds of `per` that cover n (n reaches 2^32 - 1: no sum of the two).
+constexpr uint32_t rounds_of(uint32_t n, uint32_t per) { return n / per + (n % per != 0); }
+// One lane's share of n bytes that a wave fills: put16(i) for 16 bytes at i while
+// the output is aligned to 16, put1(i) for a byte.  The counters are 64-bit: with n
+// within a stride of 2^32 a 32-bit one starts again from zero.
+template <class Put16, class Put1>
+constexpr void fill_lane(uint32_t n, bool aligned, uint32_t lane, Put16 put16, Put1 put1) {
+    const uint32_t m = aligned ? n & ~15u : 0u;
+    for (uint64_t i = 16ull * lane; i < m; i += 16 * 64) put16(uint32_t(i));
+    for (uint64_t i = uint64_t(m) + lane; i < n; i += 64) put1(uint32_t(i));
+}
+
 // Codec / dtype codes, as in zf.h.
 enum : uint8_t { C_PLAIN = 1, C_FOR_BP = 2, C_DICT_BP = 3, C_DELTA_BP = 4, C_RLE_DELTA_BP = 5, C_LZ77 = 6,
                  C_F2I_BP = 7, C_ANS = 8, C_DSTRIDE_BP = 9, C_SDICT_BP = 10, C_SDICT_ANS = 11,
