@@ -2594,6 +2594,7 @@ ZF_DEV void unit_plain(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) 
     const uint8_t *src = A.comp + ck.comp_off;
     uint8_t *dst = out_of(A, ck) + ck.out_off;
     const uint32_t a = t.a, b = min(t.b, ck.comp_len), lane = lane_id();
+    auto copy = [&](uint32_t k) { dst[k] = src[k]; };
     if (((reinterpret_cast<uintptr_t>(src + a) | reinterpret_cast<uintptr_t>(dst + a)) & 15u) == 0) {
         const uint32_t nvec = (b - a) / 16;
         const uint4 *s4 = reinterpret_cast<const uint4 *>(src + a);
@@ -2611,9 +2612,9 @@ ZF_DEV void unit_plain(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck) 
             const uint4 v = s4[i];
             st16_nt(d8 + 16ull * i, v.x, v.y, v.z, v.w);
         }
-        for (uint32_t k = a + nvec * 16 + lane; k < b; k += 64) dst[k] = src[k];
+        lane_bytes(a + nvec * 16, b, lane, copy);
     } else {
-        for (uint32_t k = a + lane; k < b; k += 64) dst[k] = src[k];
+        lane_bytes(a, b, lane, copy);
     }
 }
 

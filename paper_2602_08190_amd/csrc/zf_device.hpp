@@ -26,14 +26,19 @@ constexpr uint32_t kSdMaxToken = 64;
 
 // Rounds of `per` that cover n (n reaches 2^32 - 1: no sum of the two).
 constexpr uint32_t rounds_of(uint32_t n, uint32_t per) { return n / per + (n % per != 0); }
+// One lane's share of bytes [a, b) that a wave takes 64 at a time.  The counter is
+// 64-bit: with b within 64 of 2^32 a 32-bit one starts again from zero.
+template <class Put1>
+constexpr void lane_bytes(uint32_t a, uint32_t b, uint32_t lane, Put1 put1) {
+    for (uint64_t i = uint64_t(a) + lane; i < b; i += 64) put1(uint32_t(i));
+}
 // One lane's share of n bytes that a wave fills: put16(i) for 16 bytes at i while
-// the output is aligned to 16, put1(i) for a byte.  The counters are 64-bit: with n
-// within a stride of 2^32 a 32-bit one starts again from zero.
+// the output is aligned to 16, put1(i) for a byte.
 template <class Put16, class Put1>
 constexpr void fill_lane(uint32_t n, bool aligned, uint32_t lane, Put16 put16, Put1 put1) {
     const uint32_t m = aligned ? n & ~15u : 0u;
     for (uint64_t i = 16ull * lane; i < m; i += 16 * 64) put16(uint32_t(i));
-    for (uint64_t i = uint64_t(m) + lane; i < n; i += 64) put1(uint32_t(i));
+    lane_bytes(m, n, lane, put1);
 }
 
 // Codec / dtype codes, as in zf.h.

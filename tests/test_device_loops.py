@@ -19,14 +19,32 @@ TOP = 2**32
 SIZES = [1, 15, 16, 17, 63, 64, 1023, 1024, 1025, 65536, 100_003, TOP - 1040, TOP - 1025, TOP - 1024, TOP - 1008,
          TOP - 64, TOP - 63, TOP - 17, TOP - 16, TOP - 1]
 
-# Arguments: n, aligned, lane.  Prints the rounds of 64, the lane's 16-byte pieces
+# Arguments: first byte, end, lane: prints the lane's bytes and whether each was
+# its own; or n, aligned, lane, "fill": prints the rounds of 64, the lane's 16-byte pieces
 # and single bytes, and whether each index was its own and above the one before;
 # a loop that goes back or past n ends with "again".
 SOURCE = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "zf_device.hpp"
-int main(int, char **argv) {
+int main(int argc, char **argv) {
+    if (argc == 4) {
+        const uint32_t a = uint32_t(std::strtoull(argv[1], nullptr, 10)), lane = uint32_t(std::atoi(argv[3]));
+        const uint32_t b = uint32_t(std::strtoull(argv[2], nullptr, 10));
+        unsigned long long next = a, bytes = 0;
+        bool own = true;
+        zf::lane_bytes(a, b, lane, [&](uint32_t i) {
+            if (i < next || i >= b) {
+                std::printf("again\n");
+                std::exit(0);
+            }
+            own = own && (i - a) % 64 == lane;
+            next = i + 1ull;
+            bytes++;
+        });
+        std::printf("%llu %d\n", bytes, int(own));
+        return 0;
+    }
     const uint32_t n = uint32_t(std::strtoull(argv[1], nullptr, 10)), lane = uint32_t(std::atoi(argv[3]));
     const bool aligned = argv[2][0] == '1';
     const uint32_t m = aligned ? n & ~15u : 0u;
@@ -62,10 +80,19 @@ def test_one_byte_fill_and_step_count(program, n):
     for aligned in (1, 0):
         m = n & ~15 if aligned else 0
         for lane in (0, 1, 14, 31, 63):
-            got = subprocess.run([program, str(n), str(aligned), str(lane)], check=True, capture_output=True,
+            got = subprocess.run([program, str(n), str(aligned), str(lane), "fill"], check=True, capture_output=True,
                                  text=True, timeout=60).stdout.split()
             want = [-(-n // 64), len(range(16 * lane, m, 1024)), len(range(m + lane, n, 64)), 1]
             assert got == [str(x) for x in want], (n, aligned, lane)
+
+
+@pytest.mark.parametrize("a,b", [(0, 1), (0, 65), (8192, 16384), (TOP - 65536, TOP - 1), (TOP - 65536, TOP - 64),
+                                 (TOP - 17, TOP - 1), (TOP - 1, TOP - 1), (1, TOP - 1)])
+def test_bytes_of_a_plain_unit(program, a, b):
+    for lane in (0, 1, 16, 62, 63):
+        got = subprocess.run([program, str(a), str(b), str(lane)], check=True, capture_output=True, text=True,
+                             timeout=60).stdout.split()
+        assert got == [str(len(range(a + lane, b, 64))), "1"], lane
 
 
 @pytest.mark.gpu
