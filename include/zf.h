@@ -275,14 +275,16 @@ typedef enum {
  * is the work of one wavefront (FP: 2048-value blocks; GP: output elements;
  * PLAIN: bytes; LZ77: output bytes per block of the copy step, 4, 8 or 16,
  * one chunk per wavefront; the persistent kernel always uses 4; with neither
- * field set, launches of few chunks decode each in a workgroup's LDS; SDICT:
+ * field set, launches of few chunks decode each in a workgroup's LDS; ANS: not
+ * used, one chunk per wavefront; SDICT:
  * output bytes, in whole groups of 64 tokens),
  * `waves_per_block`
  * the wavefronts per workgroup (S/64; SDICT: at most 12, or 14 and 16, which
  * run the units over column dictionaries as two workgroups per compute unit
  * over contiguous ranges of units, each sharing an LDS copy of the hottest
  * records of a column dictionary and staging through 2 KiB buffers, and
- * the other units in a second launch of 4-wave workgroups).  A lane always owns 16 output bytes per
+ * the other units in a second launch of 4-wave workgroups; ANS: with zero,
+ * launches of few chunks run one-wave workgroups with a larger model).  A lane always owns 16 output bytes per
  * step (C).  Zero fields take the tune cache's value, else a default, made
  * smaller where a launch holds too little of the kind to fill the GPU with it
  * (a fixed rule of the launch's size). */

@@ -27,7 +27,8 @@ void launch_ans(const LaunchArgs &A, uint32_t waves, hipStream_t st) {
     // model wins; with more, the other's 19 waves a CU do, or are about even.
     // 64 KiB of flags each: 1,024 chunks 84 us fused, 143 us not; 2,048 97 and
     // 146 us; 2,304 160 and 154 us; 4,096 189 and 176 us; 16,384 729 and 703 us.
-    if (A.ans_load <= 8 * cu_count()) {
+    // Workgroups of a size that the caller set run the other.
+    if (A.ans_alone && A.ans_load <= 8 * cu_count()) {
         hipLaunchKernelGGL(k_decode_ans_fused, dim3(n), dim3(64), 0, st, A);
         return;
     }

@@ -502,6 +502,7 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
         A.counter = P->d_err + 64;
         A.fat = P->d_fat;
         A.lz_whole = !o.tiles[K_LZ].unit && !o.tiles[K_LZ].waves_per_block;
+        A.ans_alone = !o.tiles[K_ANS].waves_per_block;
     };
     fill(P->image_args);
     for (uint32_t k = 0; k < P->batches.size(); k++) {

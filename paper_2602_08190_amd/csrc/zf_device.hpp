@@ -124,6 +124,7 @@ struct LaunchArgs {
     uint32_t lz_bytes, lz_load;   // bytes of the largest LZ77 tile; of all / of the largest
     uint32_t lz_whole;            // may a workgroup decode a whole LZ77 chunk in LDS (no tile shape was asked for)?
     uint32_t ans_load;            // bytes of all ANS tiles / bytes of the largest
+    uint32_t ans_alone;           // may ANS chunks run one to a workgroup (no waves per workgroup were asked for)?
 };
 
 // Host side: a second stream, and the events that order work on it after the

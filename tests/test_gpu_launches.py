@@ -1,0 +1,54 @@
+"""Which kernels a decode launches: the tile shapes a caller sets reach their
+kernels, and the kernels chosen by size are left where the rule says so."""
+import numpy as np
+import pytest
+
+from paper_2602_08190_amd import datagen as g
+from paper_2602_08190_amd import zf
+
+from conftest import gpu_available
+from test_gpu_dispatch import ans_mix
+from test_gpu_parity import check, log, torch
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+
+def launched(cols, xs, staged=False, **kw):
+    """Names of the kernels of one decode, which is checked, and whether it
+    issued copies from the host."""
+    T = torch()
+    plan = zf.Plan(cols, device=0, **kw)
+    outs = zf.empty_outputs(cols)
+    img = None if staged else zf.upload_image(plan, cols)
+    T.cuda.synchronize()
+    act = T.profiler.ProfilerActivity
+    with T.profiler.profile(activities=[act.CUDA]) as p:
+        if staged:
+            plan.transfer_and_decompress(outs)
+        else:
+            plan.decompress_async(img, img.numel(), outs)
+        plan.sync()
+        T.cuda.synchronize()
+    keys = [e.key for e in p.key_averages()]
+    names = {k.split("(")[0].split("<")[0].split("::")[-1] for k in keys if "zf::" in k}
+    assert any(n.startswith("k_decode") for n in names), keys
+    check(cols, [o.cpu().numpy() for o in outs], xs)
+    return names, any("HtoD" in k for k in keys)
+
+
+@pytest.mark.parametrize("waves", [None, 1, 7, 16])
+def test_ans_workgroups_the_caller_sets(waves):
+    # chunks whose rings go round many times, in workgroups of one to 16 waves
+    # (16: more than 64 KiB of LDS; 16 and 7: the last workgroup part empty)
+    for size, n in ((5000, 33), (40000, 17)):
+        col, x = ans_mix(n, size)
+        log("ans", n, "chunks of", size, "waves", waves)
+        tiles = {"ANS": dict(waves_per_block=waves)} if waves else {}
+        names, _ = launched([col], [x], tiles=tiles)
+        assert names == {"k_decode_ans" if waves else "k_decode_ans_fused"}
+
+
+def test_ans_unit_alone_keeps_the_fused_model():
+    col, x = ans_mix(9, 3000)
+    names, _ = launched([col], [x], tiles={"ANS": dict(unit=1)})
+    assert names == {"k_decode_ans_fused"}
