@@ -590,6 +590,11 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
     constexpr uint32_t VPL = 16 / ES;                     // values per lane per step
     constexpr uint32_t STEPS = kForBlock / (64 * VPL);    // lane-steps per block
     constexpr uint32_t UNR = STEPS < MAXUNR ? STEPS : (MAXUNR ? MAXUNR : 1);
+    // A step of 16-byte values reads one word a lane, so those gathered from LDS
+    // take 16 steps' words at once.  136 M CHAR(16) of 25 values (the fact table's
+    // three flag columns), with 8 and 16: 475 and 460 us; 300,000 7.3 and 7.1.
+    // (From a dictionary in memory 8: 8 M of 2,000 values 24.2 us, with 16 25.0.)
+    constexpr uint32_t LDS_UNR = ES == 16 && UNR == 8 ? 16 : UNR;
     constexpr uint32_t BITS = (ES == 8 && !DICT) ? 64 : 32;
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len;
@@ -634,8 +639,8 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
         } else if constexpr (MAXUNR > 0) {
             const __amdgpu_buffer_rsrc_t rw = view(words, uint32_t(4 * nwords)), ro = view(ob, nv * ES);
             if (DICT && in_lds)
-                fp_dispatch<ES, DICT, UNR, 0, BITS, false, true>(first32(w), rw, ref, nv, ro, ro, lds, ck.dict_count,
-                                                                 bad);
+                fp_dispatch<ES, DICT, LDS_UNR, 0, BITS, false, true>(first32(w), rw, ref, nv, ro, ro, lds,
+                                                                     ck.dict_count, bad);
             else
                 fp_dispatch<ES, DICT, UNR, 0, BITS>(first32(w), rw, ref, nv, ro,
                                                     DICT ? view(dict, ck.dict_count * ES) : ro, nullptr,
