@@ -52,3 +52,20 @@ def test_ans_unit_alone_keeps_the_fused_model():
     col, x = ans_mix(9, 3000)
     names, _ = launched([col], [x], tiles={"ANS": dict(unit=1)})
     assert names == {"k_decode_ans_fused"}
+
+
+@pytest.mark.parametrize("symbols", [1, 2, 3, 5, 63, 64, 65, 255, 256])
+def test_ans_models_in_workgroups(symbols):
+    # the slot table of the model that several waves a compute unit keep: bytes
+    # whose slots begin at every place in a lane's four, equal and steep counts,
+    # bytes with one slot, alphabets that begin and end anywhere
+    r = g.rng(symbols)
+    parts = []
+    for k in range(6):
+        alphabet = np.sort(r.permutation(256)[:symbols]).astype(np.uint8)
+        p = np.ones(symbols) if k == 0 else r.random(symbols) ** (2 * k) + 1e-4
+        parts.append(r.choice(alphabet, size=1500 + 701 * k, p=p / p.sum()))
+    x = np.concatenate(parts)
+    col = zf.Column.compress(x, zf.ANS, chunk_elems=[len(p) for p in parts])
+    names, _ = launched([col], [x], tiles={"ANS": dict(waves_per_block=4)})
+    assert names == {"k_decode_ans"}
