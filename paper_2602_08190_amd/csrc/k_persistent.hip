@@ -1,5 +1,6 @@
 // The persistent multi-codec kernel, the small helper kernels and the host
 // entry that enqueues a launch's decode.
+#define ZF_UNIT_LOOP
 #include "kernels.hpp"
 #include "plan.hpp"
 
