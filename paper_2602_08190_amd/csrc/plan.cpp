@@ -514,8 +514,12 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
     }
 
     // ---- transfers by the copy kernel: the first batch's with the dictionaries
+    // (Not in a plan with the persistent kernel, whose workgroups keep every
+    // compute unit's LDS until a batch's queues are empty: the next batch's copy,
+    // which asks for the whole of one's, would begin as the decode ends.  512 MiB
+    // of LZ77 in slots of 128 MiB 6.32 ms by the kernel, 6.12 by commands.)
     std::vector<CopyPiece> pieces;
-    bool readable = !P->batches.empty();
+    bool readable = !P->batches.empty() && !P->persistent_waves;
     std::vector<const uint8_t *> dev_of(n_cols, nullptr);  // a column's bytes as the device reads them
     for (uint32_t c = 0; c < n_cols && readable; c++) {
         hipPointerAttribute_t at{};

@@ -69,3 +69,18 @@ def test_ans_models_in_workgroups(symbols):
     col = zf.Column.compress(x, zf.ANS, chunk_elems=[len(p) for p in parts])
     names, _ = launched([col], [x], tiles={"ANS": dict(waves_per_block=4)})
     assert names == {"k_decode_ans"}
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+def test_staged_copies_beside_the_persistent_kernel(persistent):
+    # a copy kernel that wants a compute unit's LDS would wait for the persistent
+    # kernel to end: that plan's copies are commands, of dictionaries too
+    xs = [g.text_column(90_001, 3), g.fixed16_column(7_003, 300, 2), g.text_column(60_001, 5),
+          g.uniform_i32(20_000, 5, 1 << 14, 1)]
+    codecs = [zf.LZ77, zf.DICT_BP, zf.SDICT_COL_ANS, zf.FOR_BP]
+    cols = [zf.Column.compress(x, c, chunk_bytes=(1 << 12, 1 << 14), seed=i, pinned=True)
+            for i, (x, c) in enumerate(zip(xs, codecs))]
+    for slot in (1 << 14, 1 << 22):
+        names, commands = launched(cols, xs, staged=True, slot_bytes=slot, persistent=persistent)
+        assert ("k_copy" in names) == (not persistent)
+        assert commands == persistent
