@@ -175,12 +175,17 @@ static void add_chunk(WorkTables &w, const zf_column &col, uint32_t ci, uint32_t
 // of 2048 values (FP), elements (GP), bytes (PLAIN, SDICT), chunks (NP).
 struct KindLoad {
     uint64_t n[K_COUNT] = {};
+    uint64_t sd_col = 0, sd_col_ans = 0;  // bytes of SDICT_COL and SDICT_COL_ANS chunks
     void add(const zf_column &col, uint32_t ci) {
         const ChunkInfo &c = col.view.chunks[ci];
         const Kind k = kind_of(c.codec, col.view.dtype);
         switch (k) {
         case K_PLAIN:
-        case K_SDICT: n[k] += c.plain_len; break;
+        case K_SDICT:
+            n[k] += c.plain_len;
+            if (c.codec == C_SDICT_COL) sd_col += c.plain_len;
+            if (c.codec == C_SDICT_COL_ANS) sd_col_ans += c.plain_len;
+            break;
         case K_RLE32:
         case K_RLE64: n[k] += c.n_elems; break;
         case K_TREE:
@@ -210,8 +215,18 @@ struct KindLoad {
 //   DSTREE output, 3 M keys 25 -> 10 us; RLE32, 300,000 dates 10.2 -> 7.0
 //   Float2Int, 300,000 doubles 36 -> 12.4 us; DICT128, 300,000 16.4 -> 13.6
 // The String-dictionary workgroups of 14 and 16 waves, which first fill an
-// LDS copy of the hottest records, pay from 1 GiB of output on (1 GiB 631 ->
-// 621 us, 2 GiB 1,265 -> 1,240; 512 MiB 264 -> 311, 256 MiB 141 -> 166).
+// LDS copy of a column dictionary's hottest records, pay for many bytes over
+// column dictionaries: those of 4 waves read faster while the entry indices
+// come from the last-level cache (256 MB), slower from memory.  Behind ANS, which
+// has just written them, the line is 832 MiB: whole decodes with 4 and 16 waves,
+// two texts, 640 MiB 477 and 534, 443 and 477 us; 768 MiB 595 and 592, 532 and 564;
+// 896 MiB 714 and 698, 642 and 628; 1 GiB 815 and 771, 747 and 712.  Without ANS
+// it is 512 MiB, where first passes gain what repeated ones lose: first passes of
+// 128 MiB 92 and 133 us, 256 172 and 165, 512 327 and 299, 768 482 and 440, 1,024
+// 635 and 577; the same decoded again 74 and 132, 134 and 158, 266 and 291, 382
+// and 428, 634 and 579.  Chunks with their own dictionary have a launch of their
+// own beside those and do not count (1 GiB of them 1,113 us when they did, 1,059).
+constexpr uint64_t kSdHotCol = 512ull << 20, kSdHotColAns = 832ull << 20;
 static uint64_t pow2_floor(uint64_t x) { return x ? uint64_t(1) << (63 - __builtin_clzll(x)) : 0; }
 static TileShape fit_tiles(TileShape t, const zf_plan_opts &o, const KindLoad &L, uint32_t cus) {
     for (uint32_t k = 0; k < K_COUNT; k++) {
@@ -222,7 +237,8 @@ static TileShape fit_tiles(TileShape t, const zf_plan_opts &o, const KindLoad &L
         }
         const bool sd = k == K_SDICT, gp = k == K_RLE32 || k == K_RLE64 || k == K_TREE;
         const bool hot = sd && t.wpb[k] >= 14;
-        if (hot && !o.tiles[k].waves_per_block && L.n[k] < (1ull << 30)) {
+        if (hot && !o.tiles[k].waves_per_block &&
+            double(L.sd_col) / kSdHotCol + double(L.sd_col_ans) / kSdHotColAns < 1.0) {
             t.wpb[k] = 4;
             if (!o.tiles[k].unit) t.unit[k] = std::min(t.unit[k], 16384u);
         }

@@ -84,3 +84,35 @@ def test_staged_copies_beside_the_persistent_kernel(persistent):
         names, commands = launched(cols, xs, staged=True, slot_bytes=slot, persistent=persistent)
         assert ("k_copy" in names) == (not persistent)
         assert commands == persistent
+
+
+def big_text(mib, codec, seed):
+    """mib MiB of one MiB of text over and over, in chunks of a MiB."""
+    x = np.tile(g.text_column(1 << 20, seed), mib)
+    return x, zf.Column.compress(x, codec, chunk_elems=[1 << 20] * mib, pinned=False)
+
+
+@pytest.mark.parametrize("parts,hot", [
+    ([(511, zf.SDICT_COL)], False), ([(512, zf.SDICT_COL)], True),
+    ([(600, zf.SDICT_COL_ANS)], False), ([(832, zf.SDICT_COL_ANS)], True),
+    ([(300, zf.SDICT_COL), (500, zf.SDICT_COL_ANS)], True),
+    ([(1024, zf.SDICT_BP), (20, zf.SDICT_COL)], False)])
+def test_sdict_workgroups_by_bytes_over_column_dictionaries(parts, hot):
+    # the 16-wave workgroups that share a copy of a column dictionary's hottest
+    # records, on both sides of their lines; own dictionaries do not count
+    T = torch()
+    log("sdict", parts)
+    xs, cols = zip(*[big_text(m, c, i) for i, (m, c) in enumerate(parts)])
+    plan = zf.Plan(list(cols), device=0)
+    img = zf.upload_image(plan, list(cols))
+    outs = zf.empty_outputs(list(cols))
+    act = T.profiler.ProfilerActivity
+    with T.profiler.profile(activities=[act.CUDA]) as p:
+        plan.decompress_async(img, img.numel(), outs)
+        plan.sync()
+        T.cuda.synchronize()
+    names = {e.key.split("(")[0].split("<")[0].split("::")[-1] for e in p.key_averages() if "zf::" in e.key}
+    assert ("k_decode_sdict_hot" in names) == hot
+    assert ("k_decode_sdict" in names) != hot
+    for x, o in zip(xs, outs):
+        assert bool((o.view(-1, 1 << 20) == T.from_numpy(x[:1 << 20]).cuda()).all())
