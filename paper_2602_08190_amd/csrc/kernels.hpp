@@ -61,11 +61,6 @@ ZF_DEV uint32_t rl32(uint32_t v, uint32_t lane) {
 ZF_DEV uint64_t rl64(uint64_t v, uint32_t lane) {
     return uint64_t(rl32(uint32_t(v), lane)) | (uint64_t(rl32(uint32_t(v >> 32), lane)) << 32);
 }
-template <class T>
-ZF_DEV T rlT(T v, uint32_t lane) {
-    if constexpr (sizeof(T) == 8) return T(rl64(uint64_t(v), lane));
-    else return T(rl32(uint32_t(v), lane));
-}
 ZF_DEV uint32_t first32(uint32_t v) { return uint32_t(__builtin_amdgcn_readfirstlane(int(v))); }
 // A pointer that every lane holds the same value of, moved to scalar
 // registers: a buffer resource built from a pointer the compiler cannot
@@ -132,20 +127,15 @@ ZF_DEV uint32_t last_nonzero_below(uint32_t x, uint32_t &carry) {
     return r;
 }
 
-ZF_DEV uint32_t wave_max32(uint32_t x) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x = max(x, uint32_t(__shfl_xor(x, d, 64)));
-    return x;
-}
 ZF_DEV bool any(bool p) { return __ballot(p) != 0; }
 
-// Orders this wave's global memory accesses for the compiler.  Lanes of one
-// wavefront share one in-order path to the L1, so a load issued after a
-// store of the same wave observes it; the fence only stops reordering.
 // Cache policy of a buffer store that bypasses the caches' normal
 // retention (the nt bit of the instruction).
 constexpr int kNonTemporal = 2;
 
+// Orders this wave's memory accesses for the compiler.  Lanes of one
+// wavefront share one in-order path to the L1, so a load issued after a
+// store of the same wave observes it; the fence only stops reordering.
 ZF_DEV void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 ZF_DEV void flag(uint32_t *err, uint32_t bits) {
@@ -193,53 +183,6 @@ ZF_DEV uint64_t mask64(uint32_t w) { return w >= 64 ? ~0ull : ((1ull << w) - 1ul
 struct Win {
     uint32_t w0, w1, w2, w3, w4;
 };
-
-// Word d (0..6) of the window; words past the fifth read as zero.
-ZF_DEV uint32_t pick(const Win &v, uint32_t d) {
-    uint32_t r = 0;
-    r = d == 0 ? v.w0 : r;
-    r = d == 1 ? v.w1 : r;
-    r = d == 2 ? v.w2 : r;
-    r = d == 3 ? v.w3 : r;
-    r = d == 4 ? v.w4 : r;
-    return r;
-}
-
-// Load the 5 packed words starting at word k0 (zero past nwords).
-ZF_DEV Win load_window(const uint32_t *words, uint64_t k0, uint64_t nwords) {
-    Win v;
-    if (k0 + 5 <= nwords) {
-        uint4 q;
-        __builtin_memcpy(&q, words + k0, 16);  // dword aligned: one dwordx4 load
-        v.w0 = q.x;
-        v.w1 = q.y;
-        v.w2 = q.z;
-        v.w3 = q.w;
-        v.w4 = words[k0 + 4];
-    } else {
-        v.w0 = k0 < nwords ? words[k0] : 0u;
-        v.w1 = k0 + 1 < nwords ? words[k0 + 1] : 0u;
-        v.w2 = k0 + 2 < nwords ? words[k0 + 2] : 0u;
-        v.w3 = k0 + 3 < nwords ? words[k0 + 3] : 0u;
-        v.w4 = k0 + 4 < nwords ? words[k0 + 4] : 0u;
-    }
-    return v;
-}
-
-// Field at bit `pos` (0 <= pos < 128) of the window, width w <= 32.
-ZF_DEV uint32_t field32(const Win &wv, uint32_t pos, uint32_t w) {
-    const uint32_t d = pos >> 5, s = pos & 31u;
-    const uint64_t pair = uint64_t(pick(wv, d)) | (uint64_t(pick(wv, d + 1)) << 32);
-    return uint32_t(pair >> s) & mask32(w);
-}
-// Field at bit `pos` (0 <= pos < 96) of the window, width w <= 64.
-ZF_DEV uint64_t field64(const Win &wv, uint32_t pos, uint32_t w) {
-    const uint32_t d = pos >> 5, s = pos & 31u;
-    const uint64_t lo = uint64_t(pick(wv, d)) | (uint64_t(pick(wv, d + 1)) << 32);
-    const uint64_t hi = pick(wv, d + 2);
-    const uint64_t v = s ? ((lo >> s) | (hi << (64 - s))) : lo;
-    return v & mask64(w);
-}
 
 // ====================================================== Fully-Parallel
 ZF_DEV uint32_t alignbit(uint32_t hi, uint32_t lo, uint32_t s) {
