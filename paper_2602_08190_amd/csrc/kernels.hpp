@@ -1,6 +1,9 @@
-// Decode routines for gfx950 (wave64), shared by the kernel translation units.  Every unit of work is owned by one
-// wavefront; waves never wait for each other, so a workgroup is just a
-// bundle of independent waves and there is no barrier anywhere.
+// Decode routines for gfx950 (wave64), shared by the kernel translation units.
+// A unit of work is owned by one wavefront, and waves do not wait for each
+// other: a workgroup is a bundle of independent waves without a barrier.  Two
+// kernels differ: eight waves of a workgroup share an LZ77 chunk (chunk_lz), with
+// barriers between their turns, and the 14- and 16-wave String-dictionary
+// workgroups meet once, when their copy of the hottest records is filled.
 //
 //  Fully-Parallel (Sec. 3.1, Sec. 4 "Scheduling Fully-Parallel"):
 //    FOR+BP and Dict+BP.  A lane owns 16 contiguous output bytes per step
@@ -27,7 +30,8 @@
 //    scans give every sequence's output and literal positions at once.  When
 //    the batch is flat (no match reads another sequence of the same batch)
 //    all literals, then all matches, are copied in lockstep; otherwise the
-//    batch is replayed in order, one sequence at a time.
+//    batch is replayed in order, one sequence at a time.  Launches of few chunks
+//    give each a workgroup and keep its output in LDS.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -548,11 +552,6 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
     constexpr uint32_t VPL = 16 / ES;                     // values per lane per step
     constexpr uint32_t STEPS = kForBlock / (64 * VPL);    // lane-steps per block
     constexpr uint32_t UNR = STEPS < MAXUNR ? STEPS : (MAXUNR ? MAXUNR : 1);
-    // A step of 16-byte values reads one word a lane, so those gathered from LDS
-    // take 16 steps' words at once.  136 M CHAR(16) of 25 values (the fact table's
-    // three flag columns), with 8 and 16: 475 and 460 us; 300,000 7.3 and 7.1.
-    // (From a dictionary in memory 8: 8 M of 2,000 values 24.2 us, with 16 25.0.)
-    constexpr uint32_t LDS_UNR = ES == 16 && UNR == 8 ? 16 : UNR;
     constexpr uint32_t BITS = (ES == 8 && !DICT) ? 64 : 32;
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t n = ck.n_elems, clen = ck.comp_len;
@@ -597,8 +596,8 @@ ZF_DEV void unit_fp(const LaunchArgs &A, const Tile &t, const ChunkDesc &ck, uin
         } else if constexpr (MAXUNR > 0) {
             const __amdgpu_buffer_rsrc_t rw = view(words, uint32_t(4 * nwords)), ro = view(ob, nv * ES);
             if (DICT && in_lds)
-                fp_dispatch<ES, DICT, LDS_UNR, 0, BITS, false, true>(first32(w), rw, ref, nv, ro, ro, lds,
-                                                                     ck.dict_count, bad);
+                fp_dispatch<ES, DICT, UNR, 0, BITS, false, true>(first32(w), rw, ref, nv, ro, ro, lds, ck.dict_count,
+                                                                 bad);
             else
                 fp_dispatch<ES, DICT, UNR, 0, BITS>(first32(w), rw, ref, nv, ro,
                                                     DICT ? view(dict, ck.dict_count * ES) : ro, nullptr,
@@ -2652,10 +2651,25 @@ ZF_DEV uint32_t xcd_block(uint32_t b, uint32_t n) {
     return x * q + min(x, r) + i;
 }
 
+// FOR and dictionary kinds keep four waves a SIMD, no more: seven or eight write
+// as many places of the output at once, which memory takes more slowly, and four
+// with enough steps' words in flight hide the loads.  Outputs of 800 MB, first as
+// many waves as their registers let in and eight steps each, then as now, tiles
+// tuned again: int32 of 1, 3, 24, 30 bits 164, 163, 271, 284 -> 135, 136, 225, 259
+// us (four steps); int64 of 3, 24, 62 bits 150, 193, 282 -> 139, 183, 267 (16);
+// int32 over 2 and 20,000 values 152, 659 -> 119, 650 (8), int64 over 2 and 200
+// 149, 154 -> 138, 142 (16); CHAR(16) of the fact table 473 -> 436 (16).  Of 132
+// MB: int32 of 1 and 30 bits 28.6, 41.5 -> 23.6, 41.2; launches of few units as
+// they were.
+template <uint32_t KIND>
+constexpr bool kFpKind = KIND == K_FOR32 || KIND == K_FOR64 || KIND == K_DICT32 || KIND == K_DICT64 ||
+                         KIND == K_DICT128;
+
 // One launch per kind: wave w of block b takes unit begin + b*waves + w.
 // Only the routine of KIND is instantiated here.
 template <uint32_t KIND>
-__global__ __launch_bounds__(1024) void k_decode_kind(LaunchArgs A) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, kFpKind<KIND> ? 4 : 8))) void k_decode_kind(
+    LaunchArgs A) {
     const uint32_t waves = blockDim.x / 64;
     // String-dictionary: the tiles of a chunk share its dictionary, so
     // neighbouring tiles go to the same XCD (and its L2)
@@ -2666,9 +2680,9 @@ __global__ __launch_bounds__(1024) void k_decode_kind(LaunchArgs A) {
     if constexpr (KIND == K_PLAIN) {
         unit_plain(A, t, ck);
     } else if constexpr (KIND == K_FOR32) {
-        unit_fp<4, false, 8>(A, t, ck);
+        unit_fp<4, false, 4>(A, t, ck);
     } else if constexpr (KIND == K_FOR64) {
-        unit_fp<8, false, 8>(A, t, ck);
+        unit_fp<8, false, 16>(A, t, ck);
     } else if constexpr (KIND == K_F2I) {
         extern __shared__ __attribute__((aligned(16))) uint8_t dict_lds[];
         unit_f2i<4>(A, t, ck, reinterpret_cast<uint32_t *>(dict_lds) + (threadIdx.x / 64) * 64);
@@ -2677,8 +2691,8 @@ __global__ __launch_bounds__(1024) void k_decode_kind(LaunchArgs A) {
         extern __shared__ __attribute__((aligned(16))) uint8_t dict_lds[];
         uint8_t *lds = dict_lds + (threadIdx.x / 64) * kDictLds;
         if constexpr (KIND == K_DICT32) unit_fp<4, true, 8>(A, t, ck, lds);
-        else if constexpr (KIND == K_DICT64) unit_fp<8, true, 8>(A, t, ck, lds);
-        else unit_fp<16, true, 8>(A, t, ck, lds);
+        else if constexpr (KIND == K_DICT64) unit_fp<8, true, 16>(A, t, ck, lds);
+        else unit_fp<16, true, 16>(A, t, ck, lds);
     } else if constexpr (KIND == K_RLE32) {
         __shared__ uint32_t rle_maps[16][64];
         if (ck.codec == C_DSTRIDE_BP) unit_rle<uint32_t, true>(A, t, ck, rle_maps[threadIdx.x / 64]);
