@@ -12,16 +12,20 @@ __global__ __launch_bounds__(64 * kLzWaves) void k_decode_lz_chunk(LaunchArgs A)
 void launch_lz(const LaunchArgs &A, uint32_t waves, uint32_t blk, hipStream_t st) {
     const uint32_t n = A.kind_begin[K_LZ + 1] - A.kind_begin[K_LZ];
     if (!n) return;
-    // The chunk kernel while its workgroups, two per compute unit for chunks of
-    // 64 KiB, come in few enough rounds: what a round takes is a chunk's latency,
-    // and the other kernel's 32 waves a compute unit make up for theirs, three
-    // and a half times that, from about four and a half rounds on.  Full 64 KiB
-    // chunks of text: 16 chunks 81 us (283 the other), 512 96 (352), 2,048 386
-    // (442), 3,072 568 (535); chunks of 16 to 64 KiB, 128 MiB 437 (416): hence
-    // the mean of the chunks and of their work in whole chunks.
-    const uint32_t out_lds = lz_head<kLzWaves>() + ((A.lz_bytes + 15) & ~15u) + 32;  // at most 73.9 KiB
-    const uint32_t slots = cu_count() * min(4u, 163840u / out_lds);
-    if (A.lz_whole && uint64_t(n) + A.lz_load <= 9ull * slots) {
+    // The chunk kernel while its workgroups, at most three per compute unit, come
+    // in few enough rounds: a round takes a chunk's latency, and the other kernel's
+    // 32 waves a compute unit make up for theirs, which is as long below 4.5 KiB and
+    // up to four times that at 64 KiB.  Text, the other kernel and this: one chunk
+    // of 4,000, 5,000, 16,000 and 65,536 bytes 14.3 and 16.8, 19.1 and 17.7, 61 and
+    // 27, 279 and 75 us; 768 of 5,000 24.2 and 23.6, 1,024 of 7,000 33.5 and 41, of
+    // 12,000 60 and 52; 1,536 of 16,000 93 and 75, 2,048 95 and 106; of 65,536 512 352
+    // and 93, 2,048 437 and 376, 2,304 472 and 441, 3,072 522 and 568.  Hence a
+    // limit of three to nine chunks per compute unit by the largest one's bytes, for
+    // the mean of the chunks and of their work in whole ones (16 to 64 KiB, 128
+    // MiB: 416 and 437 us).
+    const uint32_t out_lds = lz_head<kLzWaves>() + ((A.lz_bytes + 15) & ~15u) + 32;  // at most 72.1 KiB
+    const uint64_t per_cu = min(9u, max(3u, A.lz_bytes / 2560));
+    if (A.lz_whole && A.lz_bytes > 4608 && A.lz_bytes <= kLzMaxChunk && n + uint64_t(A.lz_load) <= 2 * per_cu * cu_count()) {
         if (out_lds > 65536)
             (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode_lz_chunk),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(out_lds));

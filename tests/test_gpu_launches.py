@@ -116,3 +116,26 @@ def test_sdict_workgroups_by_bytes_over_column_dictionaries(parts, hot):
     assert ("k_decode_sdict" in names) != hot
     for x, o in zip(xs, outs):
         assert bool((o.view(-1, 1 << 20) == T.from_numpy(x[:1 << 20]).cuda()).all())
+
+
+@pytest.mark.parametrize("size,n,chunked", [(1000, 3, False), (4608, 5, False), (4609, 5, True), (7000, 767, True),
+                                            (7000, 1024, False), (65536, 5, True), (65536, 2304, True),
+                                            (65536, 2400, False)])
+def test_lz_chunk_kernel_by_bytes_and_count(size, n, chunked):
+    # short chunks and many stay with the one-wave kernel, which is faster there
+    x = np.tile(g.text_column(min(size * n, 1 << 20), size), -(-size * n // (1 << 20)))[:size * n]
+    x = np.resize(x, size * n)
+    log("lz", n, "chunks of", size)
+    col = zf.Column.compress(x, zf.LZ77, chunk_elems=[size] * n)
+    T = torch()
+    plan = zf.Plan([col], device=0)
+    img = zf.upload_image(plan, [col])
+    outs = zf.empty_outputs([col])
+    act = T.profiler.ProfilerActivity
+    with T.profiler.profile(activities=[act.CUDA]) as p:
+        plan.decompress_async(img, img.numel(), outs)
+        plan.sync()
+        T.cuda.synchronize()
+    names = {e.key.split("(")[0].split("<")[0].split("::")[-1] for e in p.key_averages() if "zf::" in e.key}
+    assert names == {"k_decode_lz_chunk" if chunked else "k_decode_lz"}
+    assert bool((outs[0] == T.from_numpy(x).cuda()).all())
