@@ -204,7 +204,8 @@ struct KindLoad {
 // long as its units do not fill the GPU, so a kind's unit shrinks until the
 // launch has 8,192 of them or more (32 waves on each of 256 compute units; 4,096
 // for the group-parallel kinds, whose units begin with a longer prologue), and
-// a workgroup holds no more waves than leaves two workgroups per compute unit.
+// a workgroup holds no more waves than leaves two workgroups per compute unit (one,
+// where a wave takes a whole chunk).
 // Shapes the caller set stay.  Units of 256 elements, 1,024 bytes of tokens,
 // one block and 8 KiB of plain copy are the smallest: smaller ones were no
 // faster.  The DSTREE output, which the cache does not hold, takes units of at
@@ -231,8 +232,10 @@ static uint64_t pow2_floor(uint64_t x) { return x ? uint64_t(1) << (63 - __built
 static TileShape fit_tiles(TileShape t, const zf_plan_opts &o, const KindLoad &L, uint32_t cus) {
     for (uint32_t k = 0; k < K_COUNT; k++) {
         if (k == K_LZ || k == K_ANS) {  // (a unit is a whole chunk; LZ77's `unit` is its copy step's block)
-            if (!o.tiles[k].waves_per_block)
-                t.wpb[k] = uint32_t(std::clamp<uint64_t>(pow2_floor(L.n[k] / (2 * cus)), 1, t.wpb[k]));
+            // (one wave a workgroup rather than some part of the cache's: 1,024 LZ77 chunks of
+            // 10,000 bytes 47.6 us with one, 50.7 with two, 47.4 with four; 2,560 of 64
+            // KiB 473, 472 and 477)
+            if (!o.tiles[k].waves_per_block && L.n[k] < 2ull * cus * t.wpb[k]) t.wpb[k] = 1;
             continue;
         }
         const bool sd = k == K_SDICT, gp = k == K_RLE32 || k == K_RLE64 || k == K_TREE;
