@@ -2305,7 +2305,7 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 // share one stream of 16-bit words, read in byte order: at each step the lanes
 // whose state fell below L take the next words in lane order (a ballot and a
 // count of the set bits below each lane).  The stream is read once, in
-// coalesced loads one refill ahead, into a ring of kAnsRing words in the
+// coalesced loads a refill or two ahead, into a ring of kRing words in the
 // wave's LDS whose first 64 words stand after its end again, so that a step
 // reads lane by lane from a uniform offset on.
 //
@@ -2313,8 +2313,8 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 // word -> state.  What a chunk costs is that chain's latency while few waves
 // share a SIMD (an LDS read is 52 cycles, a vector instruction that uses the
 // one before it 8, any other 4), and the LDS reads per step when many do, so
-// there are two models:
-//   FUSED: one dword per slot {byte, slot - cum, f}, 16 KiB, and the ring holds
+// there are two models, one of them in two sizes:
+//   kFused: one dword per slot {byte, slot - cum, f}, 16 KiB, and the ring holds
 //     each word's entry with its top four bits beside it, looked up when the
 //     word came in.  A step then reads the entry of its new state and the entry
 //     of the next word side by side and takes one of them: one trip to the LDS.
@@ -2322,17 +2322,21 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 //     instructions stand in the order of the longest chain, the others in its
 //     gaps.  f = 4096 has no room: a chunk of one byte is filled without a
 //     table.  Eight waves fit a CU's LDS.
-//   else: slot -> byte (4 KiB) and byte -> {f, -cum} (2 KiB): two reads, but
-//     19 waves a CU.
+//   kTwo: slot -> byte (4 KiB) and byte -> {f, -cum} (2 KiB): two reads, but
+//     18 waves a CU.  kSmall is the same in 6,400 bytes of LDS, for 25 waves a CU:
+//     both halves of a byte's entry in one dword, half the ring and half the
+//     staging, whose stores of 512 bytes cost more where many 64 KiB chunks are
+//     written in step.
 // 64 KiB chunks of flags, 64 chunks: 129 us with the second, 97 us with a fused
 // model read after the word, 72 us as it is (62 ns a step); 2,048 chunks (eight
 // a CU, the LDS's reads) 148, 117 and 98 us; 4,096 chunks with the second 179.
-constexpr uint32_t kAnsRing = 512;        // words; a refill brings half of them
-constexpr uint32_t kAnsSteps = 4;         // steps between two looks at the ring (at most 64 words each)
-static_assert(kAnsSteps * kAnsLanes <= kAnsRing / 2, "ANS ring");
-
-template <bool FUSED>
+enum class Ans { kFused, kTwo, kSmall };
+template <Ans MODEL>
 ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {
+    constexpr bool FUSED = MODEL == Ans::kFused, SMALL = MODEL == Ans::kSmall;
+    constexpr uint32_t kRing = SMALL ? 256 : 512;       // words; a refill brings half of them
+    constexpr uint32_t kSteps = kRing / 2 / kAnsLanes;  // steps between two looks at it (at most 64 words each)
+    constexpr uint32_t kBlock = SMALL ? 8 : 16;         // steps whose output goes out together
     const uint8_t *s = A.comp + ck.comp_off;
     const uint32_t lane = lane_id();
     const uint32_t es = ck.dtype == D_I32 ? 4 : (ck.dtype == D_I64 || ck.dtype == D_F64) ? 8
@@ -2352,15 +2356,12 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     }
     // the shared words through a bounds-checked view of the stream, whole
     // dwords (a word past an odd end is read by a corrupt stream only); lane
-    // l of refill h loads words [256 h + 4 l, + 4)
+    // l of a refill at word h loads words [h + 4 l, + 4), or (SMALL) [h + 2 l, + 2)
+    // and, for the refill after it, [h + 128 + 2 l, + 2)
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(uniform_ptr(s + kAnsHdr)), 0, int((2 * nw + 3) & ~3u), 0x00020000);
-    uint32_t pre0, pre1;
-    auto load = [&](uint32_t at) {
-        pre0 = __builtin_amdgcn_raw_buffer_load_b32(rw, int(2 * (at + 4 * lane)), 0, 0);
-        pre1 = __builtin_amdgcn_raw_buffer_load_b32(rw, int(2 * (at + 4 * lane) + 4), 0, 0);
-    };
-    load(0);
+    auto load = [&](uint32_t word) { return __builtin_amdgcn_raw_buffer_load_b32(rw, int(2 * word), 0, 0); };
+    uint32_t pre0 = load(SMALL ? 2 * lane : 4 * lane), pre1 = load(SMALL ? 128 + 2 * lane : 4 * lane + 2);
     uint32_t x = ld32u(s + 528 + 4 * lane);  // this coder's state
     // model: lane l owns bytes 4l .. 4l + 3
     const uint32_t f2 = ld32u(s + 16 + 8 * lane), f3 = ld32u(s + 20 + 8 * lane);
@@ -2386,18 +2387,20 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     }
     uint32_t *tab = lds;                                                  // FUSED: slot -> entry
     uint8_t *sym = reinterpret_cast<uint8_t *>(lds);                      // else: slot -> byte
-    u32x2 *fc = reinterpret_cast<u32x2 *>(lds + kAnsM / 4);               // and byte -> {f, -cum}
-    uint32_t *ring = lds + (FUSED ? kAnsM : kAnsM / 4 + 512);
+    using Byte = std::conditional_t<SMALL, uint32_t, u32x2>;
+    Byte *fc = reinterpret_cast<Byte *>(lds + kAnsM / 4);                 // and byte -> {f, -cum}, or f | cum << 16
+    uint32_t *ring = lds + (FUSED ? kAnsM : kAnsM / 4 + (SMALL ? 256 : 512));
     constexpr uint32_t kWordBytes = FUSED ? 5 : 2;                        // of a ring entry
-    uint8_t *top = reinterpret_cast<uint8_t *>(ring + kAnsRing + 64);     // FUSED: each word's top four bits
-    uint8_t *stg = reinterpret_cast<uint8_t *>(ring) + (kAnsRing + 64) * kWordBytes;  // 1 KiB of output
+    uint8_t *top = reinterpret_cast<uint8_t *>(ring + kRing + 64);        // FUSED: each word's top four bits
+    uint8_t *stg = reinterpret_cast<uint8_t *>(ring) + (kRing + 64) * kWordBytes;  // kBlock x 64 bytes of output
     {
         // Slot -> byte: bit c - 1 of a 4096-bit map is set for every present
         // byte whose slots start at c > 0, so the bits below a slot count
         // its byte's rank among the present ones; row k of 64 slots is a
         // wave's lanes.  (The map and the ranked list lie where the ring and
-        // the staging will.)
-        uint32_t *list = ring, *map = ring + 256;
+        // the staging will: 1.5 KiB, or 1,280 bytes.)
+        uint32_t *list = ring, *map = ring + (FUSED ? 256 : 64);
+        uint8_t *list8 = reinterpret_cast<uint8_t *>(ring);
         map[lane] = 0;
         map[64 + lane] = 0;
         wave_fence();
@@ -2407,13 +2410,15 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         for (uint32_t k = 0; k < 4; k++) {
             const uint32_t b = 4 * lane + k;
             if (f[k]) {
-                list[rank] = FUSED ? b + (f[k] << 20) - (c << 8) : b;
+                if constexpr (FUSED) list[rank] = b + (f[k] << 20) - (c << 8);
+                else list8[rank] = uint8_t(b);
                 if (c)
                     __hip_atomic_fetch_or(map + ((c - 1) >> 5), 1u << ((c - 1) & 31u), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                 rank++;
             }
-            if constexpr (!FUSED) fc[b] = u32x2{f[k], 0u - c};
+            if constexpr (SMALL) fc[b] = f[k] | (c << 16);
+            else if constexpr (!FUSED) fc[b] = u32x2{f[k], 0u - c};
             c += f[k];
         }
         wave_fence();
@@ -2431,7 +2436,7 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
             // four slots a lane: {map word, bits before it} over the map, and the
             // three further bytes only where one of the wave's begins.  (16 rounds
             // of a dword each instead of 64 of a byte; 1 GiB of flags in chunks of
-            // 4 KiB, a model each: 924 -> 802 us; of 16 KiB 640 -> 610)
+            // 4 KiB, a model each, with kTwo: 924 -> 802 us; of 16 KiB 640 -> 610)
             u32x2 *word = reinterpret_cast<u32x2 *>(map);
             wave_fence();
             word[2 * lane] = u32x2{mlo, below};
@@ -2442,10 +2447,11 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
             for (uint32_t k = 0; k < 16; k++) {
                 const u32x2 q = word[8 * k + lane / 8];
                 const uint32_t r = q.y + uint32_t(__popc(q.x & ((1u << sh) - 1u))), t = (q.x >> sh) & 7u;
-                uint32_t v = list[r] * 0x01010101u;
+                uint32_t v = list8[r] * 0x01010101u;
                 if (any(t != 0)) {
-                    v = (v & 0xFFu) | (list[r + (t & 1u)] << 8) | (list[r + uint32_t(__popc(t & 3u))] << 16) |
-                        (list[r + uint32_t(__popc(t))] << 24);
+                    v = (v & 0xFFu) | (uint32_t(list8[r + (t & 1u)]) << 8) |
+                        (uint32_t(list8[r + uint32_t(__popc(t & 3u))]) << 16) |
+                        (uint32_t(list8[r + uint32_t(__popc(t))]) << 24);
                 }
                 reinterpret_cast<uint32_t *>(sym)[64 * k + lane] = v;
             }
@@ -2458,8 +2464,8 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(tab) + ((v << 2) & 0x3FFCu));
     };
     auto refill = [&]() {
-        // words [filled, filled + 256) into their half of the ring
-        const uint32_t at = (filled & (kAnsRing - 1)) + 4 * lane;
+        // words [filled, filled + kRing / 2) into their half of the ring
+        const uint32_t at = (filled & (kRing - 1)) + (SMALL ? 2 : 4) * lane;
         if constexpr (FUSED) {
             const u32x4 v = {entry(pre0), entry(pre0 >> 16), entry(pre1), entry(pre1 >> 16)};
             const uint32_t t = ((pre0 >> 12) & 0xFu) | ((pre0 >> 20) & 0xF00u) | ((pre1 << 4) & 0xF0000u) |
@@ -2467,30 +2473,34 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
             *reinterpret_cast<u32x4 *>(ring + at) = v;
             *reinterpret_cast<uint32_t *>(top + at) = t;
             if (at < 64) {
-                *reinterpret_cast<u32x4 *>(ring + kAnsRing + at) = v;
-                *reinterpret_cast<uint32_t *>(top + kAnsRing + at) = t;
+                *reinterpret_cast<u32x4 *>(ring + kRing + at) = v;
+                *reinterpret_cast<uint32_t *>(top + kRing + at) = t;
             }
+        } else if constexpr (SMALL) {
+            ring[at / 2] = pre0;
+            if (at < 64) ring[(kRing + at) / 2] = pre0;
         } else {
             const u32x2 v = {pre0, pre1};
             *reinterpret_cast<u32x2 *>(ring + at / 2) = v;
-            if (at < 64) *reinterpret_cast<u32x2 *>(ring + (kAnsRing + at) / 2) = v;
+            if (at < 64) *reinterpret_cast<u32x2 *>(ring + (kRing + at) / 2) = v;
         }
-        filled += kAnsRing / 2;
-        load(filled);
+        filled += kRing / 2;
+        pre0 = SMALL ? pre1 : load(filled + 4 * lane);
+        pre1 = load(SMALL ? filled + kRing / 2 + 2 * lane : filled + 4 * lane + 2);
         wave_fence();
     };
     refill();
     refill();
     uint32_t e0 = FUSED ? entry(x) : 0u, xs = x >> 12;  // FUSED: what is carried of x
     auto look = [&]() {
-        if (pos + kAnsRing / 2 > filled) refill();
+        if (pos + kRing / 2 > filled) refill();
     };
     // One byte per coder, b's low byte; then() while the reads are on their way.
     // (keep: f = 4096)
     auto step = [&](uint32_t &b, bool act, bool keep, auto &&then) {
         if constexpr (FUSED) {
             b = e0;
-            uint32_t p0 = pos & (kAnsRing - 1);
+            uint32_t p0 = pos & (kRing - 1);
             asm volatile("" : "+v"(p0));  // (the count starts from it)
             const uint32_t fx = keep ? kAnsM : b >> 20;
             const uint32_t xn = fx * (xs & 0xFFFFFFu) + ((b >> 8) & 0xFFFu);
@@ -2522,13 +2532,15 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
         } else {
             const uint32_t slot = x & (kAnsM - 1);
             b = sym[slot];
-            const u32x2 e = fc[b];
-            const uint32_t xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
+            const Byte e = fc[b];
+            uint32_t xn;
+            if constexpr (SMALL) xn = (e & 0xFFFFu) * (x >> 12) + slot - (e >> 16);
+            else xn = (e.x & 0x1FFFu) * (x >> 12) + slot + e.y;
             x = act ? xn : x;
             const bool need = act && x < kAnsL;
             const uint64_t m = __ballot(need);
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-            const uint32_t p0 = pos & (kAnsRing - 1);
+            const uint32_t p0 = pos & (kRing - 1);
             const uint32_t w = reinterpret_cast<const uint16_t *>(ring)[p0 + rank];
             uint32_t xp = (x << 16) | w;
             asm volatile("" : "+v"(xp));
@@ -2544,20 +2556,21 @@ ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) 
     const bool again = ck.col == kScratchCol;
     uint32_t t = 0;
     if ((reinterpret_cast<uintptr_t>(out) & 15u) == 0 && !single) {
-        // 16 steps at a time: each lane's 16 bytes (one per step, 64 apart)
-        // gathered in LDS, then written back as 16 contiguous bytes per lane
-        for (; t + 16 <= n / kAnsLanes; t += 16) {
+        // kBlock steps at a time: each lane's bytes (one per step, 64 apart)
+        // gathered in LDS, then written back as so many contiguous bytes per lane
+        using Piece = std::conditional_t<SMALL, u32x2, u32x4>;
+        for (; t + kBlock <= n / kAnsLanes; t += kBlock) {
 #pragma unroll
-            for (uint32_t jj = 0; jj < 16; jj++) {
+            for (uint32_t jj = 0; jj < kBlock; jj++) {
                 uint32_t b;
                 step(b, true, false, [&] {
                     stg[64 * jj + lane] = uint8_t(b);
-                    if (jj % kAnsSteps == kAnsSteps - 1) look();
+                    if (jj % kSteps == kSteps - 1) look();
                 });
             }
             wave_fence();
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + 16 * lane);
-            ZF_GLOBAL u32x4 *q = gp(reinterpret_cast<u32x4 *>(out + uint64_t(t) * kAnsLanes + 16 * lane));
+            const Piece v = reinterpret_cast<const Piece *>(stg)[lane];
+            ZF_GLOBAL Piece *q = gp(reinterpret_cast<Piece *>(out + uint64_t(t) * kAnsLanes) + lane);
             if (again) *q = v;
             else __builtin_nontemporal_store(v, q);
             wave_fence();
@@ -2637,7 +2650,7 @@ ZF_DEV void run_unit(const LaunchArgs &A, uint32_t kind, uint32_t u, uint32_t *l
         break;
     case K_LZ: unit_lz<4>(A, ck, lz_row); break;
     case K_SDICT: unit_sdict<false>(A, t, ck, lz_row); break;
-    case K_ANS: unit_ans_t<false>(A, ck, lz_row); break;
+    case K_ANS: unit_ans_t<Ans::kTwo>(A, ck, lz_row); break;
     }
 }
 

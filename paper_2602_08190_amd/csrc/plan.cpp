@@ -331,9 +331,8 @@ static void flatten(WorkTables &w, std::vector<uint8_t> &host, uint64_t off, uin
         most = w.tiles[k].empty() ? 0 : uint32_t(unit_bytes(w.chunks[w.tiles[k][0].chunk]));
         return uint32_t(sum / std::max(1u, most));
     };
-    uint32_t most;
     A.lz_load = load(K_LZ, A.lz_bytes);
-    A.ans_load = load(K_ANS, most);
+    A.ans_load = load(K_ANS, A.ans_bytes);
 }
 
 struct DeviceGuard {

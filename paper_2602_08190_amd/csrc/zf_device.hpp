@@ -19,8 +19,14 @@ constexpr uint32_t kInlineOuts = 32;
 // header of 16 + 512 (frequencies) + 256 (states) + 256 (word offsets) bytes.
 constexpr uint32_t kAnsM = 4096, kAnsL = 65536, kAnsLanes = 64, kAnsHdr = 784;
 // ANS: LDS dwords per wave: the model (4 KiB and 2 KiB, or 16 KiB fused), the
-// word ring (576 entries of 2 or 4 bytes) and 1 KiB of output staging
-constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 4096 + 576 + 144 + 256;
+// word ring (576 entries of 2 or 5 bytes) and 1 KiB of output staging; or the small
+// layout: 4 KiB and 1 KiB, 320 words and 512 bytes
+constexpr uint32_t kAnsLdsWords = 1024 + 512 + 288 + 256, kAnsLdsWordsFused = 4096 + 576 + 144 + 256,
+                   kAnsLdsWordsSmall = 1600;
+// Waves of one-wave workgroups that a compute unit holds with them (LDS is given
+// out in units of 1,280 bytes): 25 and 18
+constexpr uint32_t kAnsWavesCu = 163840 / (4 * kAnsLdsWords / 1280 * 1280 + 1280), kAnsWavesCuSmall = 163840 / 6400;
+static_assert(4 * kAnsLdsWordsSmall == 6400 && kAnsWavesCu == 18, "ANS: LDS");
 // String-dictionary: longest token
 constexpr uint32_t kSdMaxToken = 64;
 
@@ -123,7 +129,7 @@ struct LaunchArgs {
     uint8_t *outs[kInlineOuts];
     uint32_t lz_bytes, lz_load;   // bytes of the largest LZ77 tile; of all / of the largest
     uint32_t lz_whole;            // may a workgroup decode a whole LZ77 chunk in LDS (no tile shape was asked for)?
-    uint32_t ans_load;            // bytes of all ANS tiles / bytes of the largest
+    uint32_t ans_bytes, ans_load; // bytes of the largest ANS tile; of all / of the largest
     uint32_t ans_alone;           // may ANS chunks run one to a workgroup (no waves per workgroup were asked for)?
 };
 

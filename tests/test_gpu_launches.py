@@ -139,3 +139,31 @@ def test_lz_chunk_kernel_by_bytes_and_count(size, n, chunked):
     names = {e.key.split("(")[0].split("<")[0].split("::")[-1] for e in p.key_averages() if "zf::" in e.key}
     assert names == {"k_decode_lz_chunk" if chunked else "k_decode_lz"}
     assert bool((outs[0] == T.from_numpy(x).cuda()).all())
+
+
+@pytest.mark.parametrize("per_cu,more,size,kernel", [
+    (18, 0, 70, "k_decode_ans"), (18, 1, 5000, "k_decode_ans_small"), (25, 0, 130, "k_decode_ans_small"),
+    (25, 1, 90, "k_decode_ans"), (54, 1, 65, "k_decode_ans_small")])
+def test_ans_layouts_by_rounds(per_cu, more, size, kernel):
+    # the layout that lets 25 chunks run per compute unit instead of 18, where
+    # that saves a round; its ring goes round many times in chunks of 5,000
+    n = per_cu * torch().cuda.get_device_properties(0).multi_processor_count + more
+    col, x = ans_mix(n, size, exact=True)
+    log("ans", n, "chunks of", size)
+    names, _ = launched([col], [x])
+    assert names == {kernel}
+
+
+@pytest.mark.parametrize("symbols", [1, 2, 3, 5, 63, 64, 65, 255, 256])
+def test_ans_models_of_the_small_layout(symbols):
+    r = g.rng(1000 + symbols)
+    n = 19 * torch().cuda.get_device_properties(0).multi_processor_count
+    parts = []
+    for k in range(n):
+        alphabet = np.sort(r.permutation(256)[:symbols]).astype(np.uint8)
+        p = r.random(symbols) ** (1 + k % 7) + 1e-4
+        parts.append(r.choice(alphabet, size=400, p=p / p.sum()))
+    x = np.concatenate(parts)
+    col = zf.Column.compress(x, zf.ANS, chunk_elems=[400] * n)
+    names, _ = launched([col], [x])
+    assert names == {"k_decode_ans_small"}
