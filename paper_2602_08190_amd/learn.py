@@ -332,6 +332,22 @@ def evaluate(d, mask, Y, margin=0.05):
             "per_family": fam_reg, "tuned_schedule": {str(k): v for k, v in tuned.items()}}
 
 
+def provenance(a):
+    """The commands that made a report: its data's collection and its training."""
+    files = " ".join(os.path.basename(p) for p in a.data)
+    return (f"python -m paper_2602_08190_amd.learn collect --cols A B --out FILE, for each of {files}; "
+            f"python -m paper_2602_08190_amd.learn train --data {files} --weights {os.path.basename(a.weights)} "
+            f"--report {os.path.basename(a.report)} --epochs {a.epochs}")
+
+
+def describe(d):
+    """What a report's timings were measured on."""
+    n_cols, n_times = len(np.unique(d["ids"][:, 0])), int(np.isfinite(d["T"]).sum())
+    return (f"{n_cols} synthetic columns (uniform, Zipf, sorted with runs, low-cardinality, Zipf text; column "
+            f"(id // 5) % 5 == 4 held out), {len(d['X']) // n_cols} chunks of {CHUNK_BYTES >> 20} MiB each, every "
+            f"applicable (codec, schedule) timed by zf_transfer_and_decompress on one MI355X: {n_times} timings")
+
+
 def main():
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="cmd")
@@ -356,7 +372,8 @@ def main():
         rep = {"train_samples": n, "train_chunks": int(tr.sum()), "test_chunks": int(te.sum()),
                "train_seconds": round(train_s, 1), "loss_history": hist,
                "test": evaluate(d, te, predict(mean, scale, params, d["X"][te])),
-               "train": evaluate(d, tr, predict(mean, scale, params, d["X"][tr]))}
+               "train": evaluate(d, tr, predict(mean, scale, params, d["X"][tr])),
+               "command": provenance(a), "data": describe(d)}
         with open(a.report, "w") as f:
             json.dump(rep, f, indent=1)
         print(json.dumps(rep["test"]))
