@@ -25,7 +25,8 @@ void launch_lz(const LaunchArgs &A, uint32_t waves, uint32_t blk, hipStream_t st
     // MiB: 416 and 437 us).
     const uint32_t out_lds = lz_head<kLzWaves>() + ((A.lz_bytes + 15) & ~15u) + 32;  // at most 72.1 KiB
     const uint64_t per_cu = min(9u, max(3u, A.lz_bytes / 2560));
-    if (A.lz_whole && A.lz_bytes > 4608 && A.lz_bytes <= kLzMaxChunk && n + uint64_t(A.lz_load) <= 2 * per_cu * cu_count()) {
+    if (A.lz_whole && A.lz_bytes > 4608 && A.lz_bytes <= kLzMaxChunk &&
+        n + uint64_t(A.lz_load) <= 2 * per_cu * cu_count()) {
         if (out_lds > 65536)
             (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_decode_lz_chunk),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(out_lds));

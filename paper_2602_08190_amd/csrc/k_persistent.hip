@@ -58,13 +58,14 @@ __global__ void k_set_out_tab(uint8_t **tab, OutTable t, uint32_t n) {
 // workgroups, a piece each at a time, 16 KiB in flight per workgroup.  Against
 // a copy command per column range, each of which costs the host and the copy
 // engine about 10 us: a staged 16-column table of 500,009 rows in three batches
-// 826 -> 516 us (host 960 -> 130 us), 20,011 rows in one 330 -> 180 us.  16
+// 666 -> 491 us (host 960 -> 130 us), 20,011 rows in one 298 -> 140 us.  16
 // workgroups carry what the link does (1 MiB 21.5 us, a copy command 27; 8 MiB
 // 150 and 156; 256 MiB both 57 GB/s).  Each asks for a compute unit's whole
-// LDS, to share it with no wave that waits for memory in step with others:
-// loads of one compute unit return in order, and those of a decode beside the
-// copy would wait for the link's (the ANS stage 97 us alone, 150 to 207 us
-// beside the copy without this; the table 591 us).
+// LDS, to share it with no workgroup that uses LDS, as those of the kernels do
+// whose waves wait for memory in step with others (FOR and plain copies use
+// none): loads of one compute unit return in order, and those of a decode
+// beside the copy would wait for the link's (the ANS stage 97 us alone, 150 to
+// 207 us beside the copy without this; the table 582 us).
 constexpr uint32_t kCopyBlocks = 16, kCopyLds = 160 * 1024;
 __global__ __launch_bounds__(256) void k_copy(const CopyPiece *tab, uint32_t n) {
     for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {

@@ -1515,8 +1515,8 @@ ZF_DEV void unit_lz(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *row) {
 // no byte past it is written.  Matches of more than 36 bytes and those that
 // overlap themselves are copied by the whole wave one by one; a batch that is
 // not flat is replayed in order (one sequence by one).  The finished chunk is written once, in
-// aligned 16-byte stores.  64 KiB chunks of text: 283 -> 81 us for one to 256
-// of them, 128 MiB 461 -> 355 us.
+// aligned 16-byte stores.  64 KiB chunks of text: 279 -> 75 us for one, 320 -> 79
+// for 256 of them, 2,048 (128 MiB) 437 -> 376 us.
 // lds: the waves' piece lists, 3 W + 1 dwords rounded up to 16 bytes, then the
 // output laid on its 16-byte grid and 16 bytes past it.
 constexpr uint32_t kLzPieces = 256;  // a wave's list of dword copies
@@ -2327,9 +2327,9 @@ ZF_DEV void unit_sdict_hot(const LaunchArgs &A, const Tile &t, const ChunkDesc &
 //     both halves of a byte's entry in one dword, half the ring and half the
 //     staging, whose stores of 512 bytes cost more where many 64 KiB chunks are
 //     written in step.
-// 64 KiB chunks of flags, 64 chunks: 129 us with the second, 97 us with a fused
-// model read after the word, 72 us as it is (62 ns a step); 2,048 chunks (eight
-// a CU, the LDS's reads) 148, 117 and 98 us; 4,096 chunks with the second 179.
+// 64 KiB chunks of flags, 16 chunks: 125 us with kTwo, 97 us with a fused model read
+// after the word, 69 us as it is (62 ns a step alone); 2,048 chunks (eight a CU, the
+// LDS's reads) 136, 117 and 89 us; 4,096 chunks with kTwo 158.
 enum class Ans { kFused, kTwo, kSmall };
 template <Ans MODEL>
 ZF_DEV void unit_ans_t(const LaunchArgs &A, const ChunkDesc &ck, uint32_t *lds) {

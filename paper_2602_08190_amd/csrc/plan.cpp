@@ -560,10 +560,12 @@ void build_plan(zf_plan_t *P, const zf_column *const *cols, uint32_t n_cols, int
                 for (auto &cp : P->dict_copies) total += cp.len;
             // Ranges this long are left to copy commands: their cost no longer
             // counts, and a copy engine waits for no compute unit.  The table,
-            // from short ranges to long, kernel and commands: 500,009 rows 547
-            // and 738 us; 4,000,000 3.15 and 3.27 ms; 12,000,000 (ranges of
-            // about 20 MiB) 9.27 and 9.38 ms; 30,000,000 (50 MiB) 22.70 and
-            // 22.72 ms; 45,450,000 (75 MiB) 34.58 and 34.43 ms.
+            // from short ranges to long, kernel and commands: 500,009 rows 491
+            // and 666 us; 4,000,000 3.31 and 3.53 ms; 12,000,000 (ranges of
+            // about 20 MiB) 9.25 and 9.35 ms; 30,000,000 (50 MiB) 22.67 and
+            // 22.69 ms; 45,450,000 (75 MiB) 34.58 and 34.43 ms.  (Where decodes
+            // keep LDS busy the kernel waits for some: one LZ77 column of 256
+            // MiB in slots of 32 MiB 2.82 and 2.75 ms.)
             if (total >= ranges * kCopyRange) continue;
             // 64 pieces or more, of 16 to 256 KiB
             const uint64_t len = std::clamp<uint64_t>(align_up(total / 64, 16384), 16384, 262144);
