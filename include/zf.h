@@ -417,6 +417,11 @@ typedef struct {
  * `stream` waits for that signal and runs the batch's decode.  With two
  * slots the copy of batch k+1 overlaps the decode of batch k.  Outputs as in
  * zf_decompress_async.  `timing` (nullable) is filled by zf_sync.
+ * Batches of ranges under 32 MiB on average, all of them pinned, are copied by
+ * a kernel of 16 workgroups, each of which starts on a compute unit whose LDS
+ * is free: beside other work that holds LDS on every compute unit it waits for
+ * some of that to end.  Other batches, and those of plans with the persistent
+ * kernel, are copied by copy commands.
  */
 zf_status zf_transfer_and_decompress(zf_plan_t *plan, void *const *d_out, zf_stream_t stream,
                                      zf_timing *timing);
